@@ -106,4 +106,51 @@ __device__ __forceinline__ void gvals_sr(double T, double th2, double th, const 
   }
 }
 
+// The same values from the fine table in LDS: tab[p * kBoysFine + i] holds
+// coefficients 2p and 2p + 1 of interval i (four 16-byte reads, 7 for the unit
+// intervals above; neighbouring intervals sit in neighbouring banks), and behind
+// them e^{-centre} per interval, so that e^{-T} = e^{-centre} e^{-u} with
+// |u| <= 1/16 takes a degree-8 Taylor series (truncation below 5e-17) instead of
+// a range reduction.
+template <int L>
+__device__ __forceinline__ void boys_fine(double T, const double2 *__restrict__ tab, double (&F)[L + 1]) {
+  const int i = (int)(T * 8.0);
+  const double u = fma((double)i, -0.125, T) - 0.0625;
+  const double2 c0 = tab[i], c1 = tab[kBoysFine + i], c2 = tab[2 * kBoysFine + i], c3 = tab[3 * kBoysFine + i];
+  double e = 0.0;
+  if constexpr (L > 0) e = reinterpret_cast<const double *>(tab + 4 * kBoysFine)[i];
+  const double u2 = u * u, u4 = u2 * u2;
+  const double a0 = fma(c0.y, u, c0.x), a1 = fma(c1.y, u, c1.x), a2 = fma(c2.y, u, c2.x), a3 = fma(c3.y, u, c3.x);
+  F[L] = fma(fma(a3, u2, a2), u4, fma(a1, u2, a0));
+  if constexpr (L > 0) {
+    // e^{-u}: 1 - u + u^2/2 - ... + u^8/8!
+    const double b0 = 1.0 - u, b1 = fma(u, -1.0 / 6.0, 0.5), b2 = fma(u, -1.0 / 120.0, 1.0 / 24.0);
+    const double b3 = fma(u2, 1.0 / 40320.0, fma(u, -1.0 / 5040.0, 1.0 / 720.0));
+    e *= fma(fma(b3, u2, b2), u4, fma(b1, u2, b0));
+    const double t2 = 2.0 * T;
+#pragma unroll
+    for (int n = L - 1; n >= 0; --n) F[n] = fma(t2, F[n + 1], e) * (1.0 / (2 * n + 1));
+  }
+}
+template <int L>
+__device__ __forceinline__ void gvals_sr_fine(double T, double th2, double th, const double2 *__restrict__ tab,
+                                              double (&G)[L + 1]) {
+  const double x = th2 * T;
+  if (x >= kBoysSwitch) {
+#pragma unroll
+    for (int n = 0; n <= L; ++n) G[n] = 0.0;
+    return;
+  }
+  double F1[L + 1], F2[L + 1];
+  boys_fine<L>(x, tab, F2);
+  if (T < kBoysSwitch) boys_fine<L>(T, tab, F1);
+  else boys_large_e<L>(T, (L > 0) ? exp_neg(T) : 0.0, F1);
+  double f = th;
+#pragma unroll
+  for (int n = 0; n <= L; ++n) {
+    G[n] = F1[n] - f * F2[n];
+    f *= th2;
+  }
+}
+
 }  // namespace rsgdf

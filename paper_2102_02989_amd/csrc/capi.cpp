@@ -325,6 +325,64 @@ const std::vector<double> &boys_poly_table() {
   return tab;
 }
 
+// The fine table: the Taylor polynomial of degree 16 of F_L about the centre of
+// each interval of 1/8 (half width h = 1/16), economised to degree 7 by dropping
+// its Chebyshev terms of degree 8 and more (below 1e-17), then e^{-centre}.
+std::vector<double> make_boys_fine() {
+  constexpr int nd = 16, keep = 7;
+  const long double h = 0.0625L;
+  std::vector<double> tab((size_t)(kMaxL + 1) * kBoysFineTab);
+  // Chebyshev polynomials in powers, and powers in Chebyshev polynomials
+  long double tp[nd + 1][nd + 1] = {}, pt[nd + 1][nd + 1] = {};
+  tp[0][0] = tp[1][1] = 1.0L;
+  for (int n = 2; n <= nd; ++n)
+    for (int j = 0; j <= n; ++j) tp[n][j] = (j > 0 ? 2.0L * tp[n - 1][j - 1] : 0.0L) - tp[n - 2][j];
+  pt[0][0] = 1.0L;
+  for (int n = 1; n <= nd; ++n)  // x T_k = (T_{k+1} + T_{|k-1|}) / 2, x T_0 = T_1
+    for (int k = 0; k < n; ++k) {
+      const long double v = pt[n - 1][k];
+      if (k == 0) pt[n][1] += v;
+      else {
+        pt[n][k + 1] += 0.5L * v;
+        pt[n][k - 1] += 0.5L * v;
+      }
+    }
+  const int ntop = kMaxL + nd + 40;
+  std::vector<long double> F(ntop + 1);
+  for (int i = 0; i < kBoysFine; ++i) {
+    const long double T = (i + 0.5L) / 8.0L, e = expl(-T);
+    long double term = 1.0L / (2 * ntop + 1), sum = term;
+    for (int k = 1; k < 10000; ++k) {
+      term *= 2.0L * T / (2 * ntop + 2 * k + 1);
+      sum += term;
+      if (term < 1e-24L * sum) break;
+    }
+    F[ntop] = e * sum;
+    for (int n = ntop - 1; n >= 0; --n) F[n] = (2.0L * T * F[n + 1] + e) / (2 * n + 1);
+    for (int L = 0; L <= kMaxL; ++L) {
+      double *t = tab.data() + (size_t)L * kBoysFineTab;
+      long double ch[nd + 1] = {}, f = 1.0L;  // f = (-h)^j / j!
+      for (int j = 0; j <= nd; ++j) {
+        if (j > 0) f *= -h / j;
+        for (int k = 0; k <= j; ++k) ch[k] += f * F[L + j] * pt[j][k];
+      }
+      long double hj = 1.0L;
+      for (int j = 0; j <= keep; ++j) {
+        long double c = 0.0L;
+        for (int k = j; k <= keep; ++k) c += ch[k] * tp[k][j];
+        t[2 * ((size_t)(j / 2) * kBoysFine + i) + j % 2] = (double)(c / hj);
+        hj *= h;
+      }
+      t[8 * kBoysFine + i] = (double)e;
+    }
+  }
+  return tab;
+}
+const std::vector<double> &boys_fine_table() {
+  static const std::vector<double> tab = make_boys_fine();
+  return tab;
+}
+
 // ------------------------------------------------------------- screening
 struct Screen {
   double vol, dR, eps, omega;
@@ -996,7 +1054,7 @@ struct Job {
   int nk = 0, nkp = 0, npair = 0, nxs = 0, nb = 0;
   int64_t nao = 0, naux = 0, nao2 = 0, need = 0;
   double t_plan = 0.0;
-  DBuf d_ao, d_ax, d_aoe, d_aoc, d_aoc1, d_axe, d_axc, d_axc1, d_pairs, d_coff, d_nsr, d_img, d_boys, d_plist;
+  DBuf d_ao, d_ax, d_aoe, d_aoc, d_aoc1, d_axe, d_axc, d_axc1, d_pairs, d_coff, d_nsr, d_img, d_boys, d_boysf, d_plist;
   int32_t plist_grp[7] = {};  // d_plist offsets of the (l(sa), l(sb)) groups dd, dp, ds, pp, ps, ss
   DBuf d_outbuf;
   double *d_out = nullptr;
@@ -1154,6 +1212,7 @@ int Job::prepare(hipStream_t st, double mem_frac) {
   HIPCHK(upload(d_img, hp.img, st));
   const std::vector<double> boys = boys_poly_table();
   HIPCHK(upload(d_boys, boys, st));
+  HIPCHK(upload(d_boysf, boys_fine_table(), st));
 
   if (logging || tune) {
     d_out = nullptr;  // magnitude logging and tuning trials write no output
@@ -1336,7 +1395,7 @@ int Job::prepare(hipStream_t st, double mem_frac) {
       const int lab = sA.l + sB.l, nkx = (sP.l / 2 + 1) * (sP.l / 2 + 1) * (sP.l / 2 + 1);
       const int nblk = ncart_h(sP.l) * ncart_h(sA.l) * ncart_h(sB.l);
       const double ev = 2.0 * nherm(Lt) + 2.0 * ncart_h(sP.l) * nherm(lab) * nkx + 2.0 * nblk * nherm(lab);
-      const double nranges = std::ceil((double)nk / std::min(nk, sr_cells_per_wave(nblk)));
+      const double nranges = std::ceil((double)nk / std::min(nk, sr_cells_per_wave(sP.l, sA.l, sB.l)));
       est[t] = (double)sA.nprim * sB.nprim * sP.nprim * (double)nimg * (nm * sr_term_flops(Lt) + 13.6 * nranges * ev);
     }, 1024);
     double tot = 0.0;
@@ -1360,7 +1419,12 @@ int Job::prepare(hipStream_t st, double mem_frac) {
           const int64_t want = std::max<int64_t>(1, (int64_t)std::ceil(est[t] / target));
           const int nsplit = (int)std::min<int64_t>(want, nk);
           int ncbw = (nk + nsplit - 1) / nsplit;
-          ncbw = std::min(ncbw, sr_cells_per_wave(nblk));  // lane groups per wave (LDS accumulators)
+          const int lP = hp.ax[tr.aux].l, la = hp.ao[pp.sa].l, lb = hp.ao[pp.sb].l;
+          // one unit per lane: a wave takes 64 / ncbw images of a class at a time, so
+          // a cell range narrower than that leaves lanes empty
+          if (sr_unit_class(lP, la, lb))
+            ncbw = std::max<int>(ncbw, (int)std::min<int64_t>(nk, 64 * (int64_t)nk / std::max<int64_t>(nimg_pair[tr.pair], 1)));
+          ncbw = std::min(ncbw, sr_cells_per_wave(lP, la, lb));  // BvK cells per wave
           const int nranges = (nk + ncbw - 1) / ncbw;
           int nsl = (int)std::min<int64_t>(64, (want + nranges - 1) / nranges);
           if (nsl > 1 && part_bytes + (double)nsl * nk * nk * nblk * 8.0 > part_budget) nsl = 1;
@@ -1470,6 +1534,7 @@ int Job::prepare(hipStream_t st, double mem_frac) {
   base.ncell_nf = hp.scr.ncell_nf;
   base.ncell_r0 = hp.scr.r0;
   base.boys = d_boys.as<double>();
+  base.boys_fine = d_boysf.as<double>();
   base.acut = acut;
   base.X = d_X.as<double>();
   base.nao = (int32_t)nao;
@@ -3049,7 +3114,7 @@ int rsgdf_plan_features_acut(const rsgdf_cell *cell, const rsgdf_basis *basis, c
       const int lab = sA.l + sB.l, nkx = (sP.l / 2 + 1) * (sP.l / 2 + 1) * (sP.l / 2 + 1);
       const int nblk = ncart_h(sP.l) * ncart_h(sA.l) * ncart_h(sB.l);
       const double ev = 2.0 * nherm(Lt) + 2.0 * ncart_h(sP.l) * nherm(lab) * nkx + 2.0 * nblk * nherm(lab);
-      const double nranges = std::ceil((double)nk / std::min(nk, sr_cells_per_wave(nblk)));
+      const double nranges = std::ceil((double)nk / std::min(nk, sr_cells_per_wave(sP.l, sA.l, sB.l)));
       const double npp = (double)sA.nprim * sB.nprim - (double)ndiff(sA, hp.ao_exp) * ndiff(sB, hp.ao_exp);
       const double np3 = npp * (sP.nprim - ndiff(sP, hp.ax_exp)) * (double)nimg;
       sr += np3 * (nm * sr_term_flops(Lt) + 13.6 * nranges * ev);

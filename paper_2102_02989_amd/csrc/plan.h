@@ -19,6 +19,11 @@ constexpr double kBoysSwitch = 36.0;           // polynomial table below, asympt
 constexpr int kBoysIntervals = 36;             // unit intervals of T in [0, 36)
 constexpr int kBoysPolyDeg = 12;               // Taylor degree about each interval centre
 
+// Fine table of the one-unit-per-lane kernels: degree-7 polynomials on intervals
+// of 1/8, stored [coefficient pair][interval], then e^{-centre} [interval].
+constexpr int kBoysFine = 288;                     // intervals of T in [0, 36)
+constexpr int kBoysFineTab = 9 * kBoysFine;        // doubles per order L
+
 __host__ __device__ constexpr int ncart(int l) { return (l + 1) * (l + 2) / 2; }
 
 // Angular growth of an AO pair factor in the screening windows (Eqs.
@@ -38,7 +43,20 @@ constexpr int kMaxCellsPerWave = 8;  // BvK cells (lane groups) per wave
 __host__ __device__ constexpr int sr_max_cells(int nblk) {
   return (kBlkCap / nblk) < 1 ? 1 : ((kBlkCap / nblk) > kMaxCellsPerWave ? kMaxCellsPerWave : kBlkCap / nblk);
 }
-inline int sr_cells_per_wave(int nblk) { return sr_max_cells(nblk); }
+// Aux Hermite orders tau that a shell of angular momentum lP expands into:
+// |tau| = lP, then |tau| = lP - 2 (single-centre coefficients keep the parity).
+__host__ __device__ constexpr int sr_ntau(int lP) { return ncart(lP) + (lP >= 2 ? ncart(lP - 2) : 0); }
+// Classes of the one-unit-per-lane kernel: a lane's sums over the aux Hermite
+// orders and the AO components stay in its registers (126 doubles are half of
+// a one-wave register file, the rest holds the Hermite integrals).
+constexpr int kUnitAccMax = 126;
+__host__ __device__ constexpr bool sr_unit_class(int lP, int la, int lb) {
+  return sr_ntau(lP) * ncart(la) * ncart(lb) <= kUnitAccMax;
+}
+// most BvK cells of one wave
+inline int sr_cells_per_wave(int lP, int la, int lb) {
+  return sr_unit_class(lP, la, lb) ? kMaxCellsPerWave : sr_max_cells(ncart(lP) * ncart(la) * ncart(lb));
+}
 // AO pair class of (l_a, l_b), l_a >= l_b: 0 ss, 1 ps, 2 pp, 3 ds, 4 dp, 5 dd
 inline int pair_class(int la, int lb) {
   static const int t[3][3] = {{0, -1, -1}, {1, 2, -1}, {3, 4, 5}};
@@ -161,6 +179,7 @@ struct SRParams {
   double omega, eps, dR;
   double ncell_nf, ncell_r0;  // N_cell model of Eq. S19
   const double *boys;       // [L = 0..kMaxL][kBoysIntervals][kBoysPolyDeg + 1]
+  const double *boys_fine;  // [L = 0..kMaxL][kBoysFineTab]
   double acut;              // > 0: compact/diffuse split (primitive triples with a diffuse aux
                             // primitive or two diffuse AO primitives are left to Eq. M15)
   double *X;                // [Nk][Nk][naux_b][nao][nao]
