@@ -210,58 +210,73 @@ hipError_t launch_fold(const FoldParams &fp, hipStream_t stream) {
 // with the Hermite expansion: overlap = K (pi/p)^{3/2} E^x_0 E^y_0 E^z_0.
 
 
+// One wave per (pair, cell): the lanes take the (image, primitive pair) terms of
+// the cell in turn and a butterfly adds their sums (the same bits on every
+// lane, in a fixed order).  One thread per (pair, cell), as this kernel used to
+// be, is a chain of all the cell's terms: 2.4 ms at Gamma (21 pairs of a 2-atom
+// cell, up to 250 images x 9 primitive pairs each) and 6.8 ms for a 3-atom
+// double-zeta cell on a 1x3x2 mesh, against at most 0.06 ms in this form, where the longest
+// lane has one or a few dozen terms.
 template <int LA, int LB>
-__device__ void ovl_pair_class(const OvlParams &op, int ip, int c) {
+__device__ void ovl_pair_class(const OvlParams &op, const Pair &pr, const Shell &sA, const Shell &sB, int ip, int c,
+                               int lane) {
   constexpr int NCA = ncart(LA), NCB = ncart(LB);
-  const Pair pr = op.pairs[ip];
-  const Shell sA = op.ao[pr.sa], sB = op.ao[pr.sb];
   double acc[NCA * NCB];
 #pragma unroll
   for (int i = 0; i < NCA * NCB; ++i) acc[i] = 0.0;
   const int beg = op.cls_off[pr.cls_off + c], end = op.cls_off[pr.cls_off + c + 1];
-  for (int ii = beg; ii < end; ++ii) {
-    const double *nv = op.img + 3 * (size_t)(pr.img_off + ii);
+  const int npp = sA.nprim * sB.nprim;
+  const int64_t nterm = (int64_t)(end - beg) * npp;
+  for (int64_t t = lane; t < nterm; t += 64) {
+    const int im = (int)(t / npp), pp = (int)(t - (int64_t)im * npp);
+    const int ka = pp / sB.nprim, kb = pp - ka * sB.nprim;
+    const double *nv = op.img + 3 * ((size_t)pr.img_off + beg + im);
     const double Bx = sB.x + nv[0], By = sB.y + nv[1], Bz = sB.z + nv[2];
     const double r2 = (sA.x - Bx) * (sA.x - Bx) + (sA.y - By) * (sA.y - By) + (sA.z - Bz) * (sA.z - Bz);
-    for (int ka = 0; ka < sA.nprim; ++ka)
-      for (int kb = 0; kb < sB.nprim; ++kb) {
-        const double ga = op.ao_exp[sA.pptr + ka], gb = op.ao_exp[sB.pptr + kb];
-        if (op.acut > 0.0 && ga < op.acut && gb < op.acut) continue;  // a diffuse-diffuse pair: Eq. M15
-        const double p = ga + gb, oop = 1.0 / p;
-        const double arg = ga * gb * oop * r2;
-        if (arg > 46.0) continue; /* e^{-46} ~ 1e-20 */
-        const double K = exp(-arg) * op.ao_coef[sA.pptr + ka] * op.ao_coef[sB.pptr + kb] * kPi * oop * sqrt(kPi * oop);
-        const double Px = (ga * sA.x + gb * Bx) * oop, Py = (ga * sA.y + gb * By) * oop, Pz = (ga * sA.z + gb * Bz) * oop;
-        double Ex[LA + 1][LB + 1][LA + LB + 1], Ey[LA + 1][LB + 1][LA + LB + 1], Ez[LA + 1][LB + 1][LA + LB + 1];
-        hermite_E<LA, LB>(Px - sA.x, Px - Bx, 0.5 * oop, Ex);
-        hermite_E<LA, LB>(Py - sA.y, Py - By, 0.5 * oop, Ey);
-        hermite_E<LA, LB>(Pz - sA.z, Pz - Bz, 0.5 * oop, Ez);
+    const double ga = op.ao_exp[sA.pptr + ka], gb = op.ao_exp[sB.pptr + kb];
+    if (op.acut > 0.0 && ga < op.acut && gb < op.acut) continue;  // a diffuse-diffuse pair: Eq. M15
+    const double p = ga + gb, oop = 1.0 / p;
+    const double arg = ga * gb * oop * r2;
+    if (arg > 46.0) continue; /* e^{-46} ~ 1e-20 */
+    const double K = exp(-arg) * op.ao_coef[sA.pptr + ka] * op.ao_coef[sB.pptr + kb] * kPi * oop * sqrt(kPi * oop);
+    const double Px = (ga * sA.x + gb * Bx) * oop, Py = (ga * sA.y + gb * By) * oop, Pz = (ga * sA.z + gb * Bz) * oop;
+    double Ex[LA + 1][LB + 1][LA + LB + 1], Ey[LA + 1][LB + 1][LA + LB + 1], Ez[LA + 1][LB + 1][LA + LB + 1];
+    hermite_E<LA, LB>(Px - sA.x, Px - Bx, 0.5 * oop, Ex);
+    hermite_E<LA, LB>(Py - sA.y, Py - By, 0.5 * oop, Ey);
+    hermite_E<LA, LB>(Pz - sA.z, Pz - Bz, 0.5 * oop, Ez);
 #pragma unroll
-        for (int ia = 0; ia < NCA; ++ia)
+    for (int ia = 0; ia < NCA; ++ia)
 #pragma unroll
-          for (int ib = 0; ib < NCB; ++ib)
-            acc[ia * NCB + ib] += K * Ex[cart_lx(LA, ia)][cart_lx(LB, ib)][0] * Ey[cart_ly(LA, ia)][cart_ly(LB, ib)][0] *
-                                  Ez[cart_lz(LA, ia)][cart_lz(LB, ib)][0];
-      }
+      for (int ib = 0; ib < NCB; ++ib)
+        acc[ia * NCB + ib] += K * Ex[cart_lx(LA, ia)][cart_lx(LB, ib)][0] * Ey[cart_ly(LA, ia)][cart_ly(LB, ib)][0] *
+                              Ez[cart_lz(LA, ia)][cart_lz(LB, ib)][0];
   }
   double *dst = op.O + ((size_t)ip * op.nk + c) * 36;
 #pragma unroll
-  for (int i = 0; i < NCA * NCB; ++i) dst[i] = acc[i];
+  for (int i = 0; i < NCA * NCB; ++i) {
+    double v = acc[i];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (lane == 0) dst[i] = v;
+  }
 }
 
-__global__ void ovl_kernel(const OvlParams op) {
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+constexpr int kOvlWaves = 4;  // waves per workgroup
+
+__global__ __launch_bounds__(64 * kOvlWaves) void ovl_kernel(const OvlParams op) {
+  const int64_t gid = (int64_t)blockIdx.x * kOvlWaves + (threadIdx.x >> 6);
   if (gid >= (int64_t)op.npair * op.nk) return;
+  const int lane = threadIdx.x & 63;
   const int ip = (int)(gid / op.nk), c = (int)(gid % op.nk);
   const Pair pr = op.pairs[ip];
-  const int la = op.ao[pr.sa].l, lb = op.ao[pr.sb].l;
-  switch (la * 3 + lb) {
-    case 0: ovl_pair_class<0, 0>(op, ip, c); break;
-    case 3: ovl_pair_class<1, 0>(op, ip, c); break;
-    case 4: ovl_pair_class<1, 1>(op, ip, c); break;
-    case 6: ovl_pair_class<2, 0>(op, ip, c); break;
-    case 7: ovl_pair_class<2, 1>(op, ip, c); break;
-    case 8: ovl_pair_class<2, 2>(op, ip, c); break;
+  const Shell sA = op.ao[pr.sa], sB = op.ao[pr.sb];
+  switch (sA.l * 3 + sB.l) {
+    case 0: ovl_pair_class<0, 0>(op, pr, sA, sB, ip, c, lane); break;
+    case 3: ovl_pair_class<1, 0>(op, pr, sA, sB, ip, c, lane); break;
+    case 4: ovl_pair_class<1, 1>(op, pr, sA, sB, ip, c, lane); break;
+    case 6: ovl_pair_class<2, 0>(op, pr, sA, sB, ip, c, lane); break;
+    case 7: ovl_pair_class<2, 1>(op, pr, sA, sB, ip, c, lane); break;
+    case 8: ovl_pair_class<2, 2>(op, pr, sA, sB, ip, c, lane); break;
     default: break;
   }
 }
@@ -298,8 +313,9 @@ __global__ void smn_kernel(const SmnParams sp) {
 }
 
 hipError_t launch_overlaps(const OvlParams &op, const SmnParams &sp, hipStream_t stream) {
-  int64_t n1 = (int64_t)op.npair * op.nk;
-  hipLaunchKernelGGL(ovl_kernel, dim3((unsigned)((n1 + 127) / 128)), dim3(128), 0, stream, op);
+  const int64_t n1 = (int64_t)op.npair * op.nk;
+  hipLaunchKernelGGL(ovl_kernel, dim3((unsigned)((n1 + kOvlWaves - 1) / kOvlWaves)), dim3(64 * kOvlWaves), 0, stream,
+                     op);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   int64_t n2 = (int64_t)sp.npair * sp.nk * 36;
