@@ -1,12 +1,15 @@
 // df.hip -- the density-fitting solve of Eq. M4 on gfx950:
 //     sum_Q J^{k12}_PQ d^{k1k2}_{Q mu nu} = V^{k1k2}_{P mu nu}   for every k-pair,
 // with J^k Hermitian positive definite (a Coulomb metric with q = 0 removed).
-// Per k of the mesh (one workgroup each, the matrices are a few MB and stay in
-// L2):
-//   1. Cholesky factor J = L L^H (left-looking, column by column: the rows
-//      below the diagonal in parallel, each summing over the columns already
-//      done; the diagonal by a fixed-order reduction through LDS);
-//   2. W = L^{-1} by forward substitution, one column of W per thread.
+// Per k of the mesh, all k in the same launches, in blocks of 64:
+//   1. Cholesky factor J = L L^H, right-looking: the diagonal block and its
+//      inverse by one workgroup in LDS, the panel below it and the trailing
+//      blocks as 64 x 64 x 64 complex products on the FP64 matrix cores;
+//   2. W = L^{-1} block row by block row, a strip of 16 columns per workgroup.
+// Bound by the chain of n / 64 steps, not by operations: 420 functions on a
+// 2x2x2 mesh took 26.6 ms with one workgroup per k column by column and one
+// thread per column of W, and take 1.3 ms in this form (0.8 ms of it the seven
+// diagonal blocks, whose 64 dependent columns are the chain).
 // Then for every k-pair Y = W V and d = W^H Y (the forward and backward
 // substitutions of L L^H d = V as products with the substituted inverse, which
 // keeps the error of two triangular solves) as complex FP64 matrix products on
@@ -20,118 +23,245 @@
 
 namespace rsgdf {
 
-constexpr int kCholThreads = 1024;
+typedef double df_d4 __attribute__((ext_vector_type(4)));
+constexpr int FB = 64;         // block of the factorisation
+constexpr int FBP = FB + 1;    // LDS row stride (doubles): rows start in distinct banks
 
-// J [nk][n][n] complex (read: lower triangle), L [nk][n][n] complex (written:
-// lower triangle incl. diagonal; the strict upper triangle is zeroed), bad [nk]
-__global__ __launch_bounds__(kCholThreads) void chol_kernel(const double *__restrict__ J, double *__restrict__ L,
-                                                            int n, int *__restrict__ bad) {
-  __shared__ double red[kCholThreads];
-  __shared__ double rowj[2 * 1024];  // L[j][0..j) of the current column, in chunks of 1024
-  __shared__ double sdiag;
-  const int k = blockIdx.x, tid = threadIdx.x;
-  const double *Jk = J + 2 * (size_t)k * n * n;
-  double *Lk = L + 2 * (size_t)k * n * n;
-  for (size_t i = tid; i < (size_t)n * n; i += kCholThreads) {
-    const size_t r = i / n, c = i % n;
-    Lk[2 * i] = (c <= r) ? Jk[2 * i] : 0.0;
-    Lk[2 * i + 1] = (c < r) ? Jk[2 * i + 1] : 0.0;
-  }
-  __syncthreads();
-  int failed = 0;
-  for (int j = 0; j < n; ++j) {
-    // diagonal: J_jj - sum_{c<j} |L_jc|^2, partial sums per thread then a tree
-    double s = 0.0;
-    for (int c = tid; c < j; c += kCholThreads) {
-      const double xr = Lk[2 * ((size_t)j * n + c)], xi = Lk[2 * ((size_t)j * n + c) + 1];
-      s += xr * xr + xi * xi;
-    }
-    red[tid] = s;
-    __syncthreads();
-    for (int w = kCholThreads / 2; w >= 1; w >>= 1) {
-      if (tid < w) red[tid] += red[tid + w];
-      __syncthreads();
-    }
-    if (tid == 0) {
-      const double jj = Lk[2 * ((size_t)j * n + j)];
-      const double dj = jj - red[0];
-      if (!(dj > 1e-12 * jj)) failed = 1;
-      sdiag = (dj > 0.0) ? sqrt(dj) : 1.0;
-      Lk[2 * ((size_t)j * n + j)] = sdiag;
-      Lk[2 * ((size_t)j * n + j) + 1] = 0.0;
-    }
-    __syncthreads();
-    const double inv = 1.0 / sdiag;
-    // rows i > j: (J_ij - sum_{c<j} L_ic conj(L_jc)) / L_jj, row j staged in LDS
-    for (int i0 = j + 1; i0 < n; i0 += kCholThreads) {
-      const int i = i0 + tid;
-      double ar = 0.0, ai = 0.0;
-      if (i < n) {
-        ar = Lk[2 * ((size_t)i * n + j)];
-        ai = Lk[2 * ((size_t)i * n + j) + 1];
-      }
-      for (int c0 = 0; c0 < j; c0 += 1024) {
-        const int cn = (j - c0 < 1024) ? j - c0 : 1024;
-        __syncthreads();
-        for (int c = tid; c < cn; c += kCholThreads) {
-          rowj[2 * c] = Lk[2 * ((size_t)j * n + c0 + c)];
-          rowj[2 * c + 1] = Lk[2 * ((size_t)j * n + c0 + c) + 1];
-        }
-        __syncthreads();
-        if (i < n) {
-          const double *Li = Lk + 2 * ((size_t)i * n + c0);
-          for (int c = 0; c < cn; ++c) {
-            const double lr = Li[2 * c], li = Li[2 * c + 1], jr = rowj[2 * c], ji = rowj[2 * c + 1];
-            // L_ic conj(L_jc)
-            ar -= lr * jr + li * ji;
-            ai -= li * jr - lr * ji;
-          }
-        }
-      }
-      if (i < n) {
-        Lk[2 * ((size_t)i * n + j)] = ar * inv;
-        Lk[2 * ((size_t)i * n + j) + 1] = ai * inv;
-      }
-    }
-    __syncthreads();
-  }
-  if (tid == 0) bad[k] = failed;
+// L = lower triangle of J (strict upper zero), W = 0, bad = 0
+__global__ __launch_bounds__(256) void df_init_kernel(const double2 *__restrict__ J, double2 *__restrict__ L,
+                                                      double2 *__restrict__ W, int n, int64_t total,
+                                                      int *__restrict__ bad, int nk) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < nk) bad[i] = 0;
+  if (i >= total) return;
+  const int64_t e = i % ((int64_t)n * n);
+  const int r = (int)(e / n), c = (int)(e % n);
+  double2 v = make_double2(0.0, 0.0);
+  if (c <= r) v = J[i];
+  if (c == r) v.y = 0.0;
+  L[i] = v;
+  W[i] = make_double2(0.0, 0.0);
 }
 
-// W = L^{-1} (lower triangular), one column of W per thread:
-//   W_jj = 1/L_jj,  W_ij = -(sum_{c=j}^{i-1} L_ic W_cj) / L_ii  (i > j).
-// W [nk][n][n] complex, strict upper triangle zeroed.
-__global__ __launch_bounds__(256) void trinv_kernel(const double *__restrict__ L, double *__restrict__ W, int n) {
-  const int k = blockIdx.y;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  const double *Lk = L + 2 * (size_t)k * n * n;
-  double *Wk = W + 2 * (size_t)k * n * n;
-  for (int i = 0; i < j; ++i) {
-    Wk[2 * ((size_t)i * n + j)] = 0.0;
-    Wk[2 * ((size_t)i * n + j) + 1] = 0.0;
+// Diagonal block p of every k: Cholesky factor and its inverse in LDS (one
+// workgroup per k).  A pivot below 1e-12 of its diagonal entry of J marks k.
+__global__ __launch_bounds__(256) void df_diag_kernel(const double *__restrict__ J, double *__restrict__ L,
+                                                      double *__restrict__ W, int n, int p, int *__restrict__ bad) {
+  __shared__ double ar[FB][FBP], ai[FB][FBP], wr[FB][FBP], wi[FB][FBP];
+  const int k = blockIdx.x, tid = threadIdx.x;
+  const int p0 = p * FB, nb = min(FB, n - p0);
+  double *Lk = L + 2 * (size_t)k * n * n, *Wk = W + 2 * (size_t)k * n * n;
+  const double *Jk = J + 2 * (size_t)k * n * n;
+  for (int e = tid; e < FB * FB; e += 256) {
+    const int r = e / FB, c = e % FB;
+    const bool in = r < nb && c <= r;
+    const size_t o = 2 * ((size_t)(p0 + r) * n + p0 + c);
+    ar[r][c] = in ? Lk[o] : 0.0;
+    ai[r][c] = in ? Lk[o + 1] : 0.0;
+    wr[r][c] = wi[r][c] = 0.0;
   }
-  Wk[2 * ((size_t)j * n + j)] = 1.0 / Lk[2 * ((size_t)j * n + j)];
-  Wk[2 * ((size_t)j * n + j) + 1] = 0.0;
-  for (int i = j + 1; i < n; ++i) {
-    double sr = 0.0, si = 0.0;
-    const double *Li = Lk + 2 * (size_t)i * n;
-    for (int c = j; c < i; ++c) {
-      const double lr = Li[2 * c], li = Li[2 * c + 1];
-      const double wr = Wk[2 * ((size_t)c * n + j)], wi = Wk[2 * ((size_t)c * n + j) + 1];
-      sr += lr * wr - li * wi;
-      si += lr * wi + li * wr;
+  int failed = 0;
+  const int tx = tid & 15, ty = tid >> 4;
+  for (int j = 0; j < nb; ++j) {
+    __syncthreads();
+    const double d = ar[j][j];
+    if (tid == 0 && !(d > 1e-12 * Jk[2 * ((size_t)(p0 + j) * n + p0 + j)])) failed = 1;
+    const double s = (d > 0.0) ? sqrt(d) : 1.0, inv = 1.0 / s;
+    __syncthreads();
+    if (tid > j && tid < nb) {
+      ar[tid][j] *= inv;
+      ai[tid][j] *= inv;
     }
-    const double d = 1.0 / Li[2 * i];
-    Wk[2 * ((size_t)i * n + j)] = -sr * d;
-    Wk[2 * ((size_t)i * n + j) + 1] = -si * d;
+    if (tid == j) ar[j][j] = s;
+    __syncthreads();
+    for (int i = j + 1 + ty; i < nb; i += 16)
+      for (int c = j + 1 + tx; c <= i; c += 16) {
+        const double xr = ar[i][j], xi = ai[i][j], yr = ar[c][j], yi = ai[c][j];
+        ar[i][c] -= xr * yr + xi * yi;  // L_ij conj(L_cj)
+        if (c < i) ai[i][c] -= xi * yr - xr * yi;
+      }
+  }
+  if (tid == 0 && failed) bad[k] = 1;
+  // rows of the inverse: four threads per column share the sum over c
+  const int j = tid >> 2, part = tid & 3;
+  for (int i = 0; i < nb; ++i) {
+    __syncthreads();
+    double sr = 0.0, si = 0.0;
+    for (int c = j + part; c < i; c += 4) {
+      const double xr = ar[i][c], xi = ai[i][c], yr = wr[c][j], yi = wi[c][j];
+      sr += xr * yr - xi * yi;
+      si += xr * yi + xi * yr;
+    }
+#pragma unroll
+    for (int o = 1; o < 4; o <<= 1) {
+      sr += __shfl_xor(sr, o, 64);
+      si += __shfl_xor(si, o, 64);
+    }
+    const double inv = 1.0 / ar[i][i];
+    if (part == 0 && j <= i) {
+      wr[i][j] = (j == i) ? inv : -sr * inv;
+      wi[i][j] = (j == i) ? 0.0 : -si * inv;
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < FB * FB; e += 256) {
+    const int r = e / FB, c = e % FB;
+    if (r >= nb || c > r) continue;
+    const size_t o = 2 * ((size_t)(p0 + r) * n + p0 + c);
+    Lk[o] = ar[r][c];
+    Lk[o + 1] = ai[r][c];
+    Wk[o] = wr[r][c];
+    Wk[o + 1] = wi[r][c];
+  }
+}
+
+// X Y^H of two 64 x 64 blocks in LDS; wave w holds rows [16 w, 16 w + 16), its
+// four 16-column tiles in cre/cim (result D[lg + 4 v][li])
+__device__ __forceinline__ void df_xyh(const double (&xr)[FB][FBP], const double (&xi)[FB][FBP],
+                                       const double (&yr)[FB][FBP], const double (&yi)[FB][FBP], df_d4 (&cre)[4],
+                                       df_d4 (&cim)[4]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lg = lane >> 4;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) cre[c][v] = cim[c][v] = 0.0;
+#pragma unroll 4
+  for (int ks = 0; ks < FB / 4; ++ks) {
+    const int t = 4 * ks + lg;
+    const double a_r = xr[16 * wave + li][t], a_i = xi[16 * wave + li][t];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const double b_r = yr[16 * c + li][t], b_i = yi[16 * c + li][t];
+      // (a_r + i a_i)(b_r - i b_i)
+      cre[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_r, b_r, cre[c], 0, 0, 0);
+      cre[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_i, b_i, cre[c], 0, 0, 0);
+      cim[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_i, b_r, cim[c], 0, 0, 0);
+      cim[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a_r, b_i, cim[c], 0, 0, 0);
+    }
+  }
+}
+
+// Blocks below the diagonal block p (PANEL): L_ip = A_ip W_pp^H.  Then the
+// trailing blocks i >= k > p: A_ik -= L_ip L_kp^H.  Grid (nk, row block, column
+// block); every block is read and written by one workgroup.
+template <bool PANEL>
+__global__ __launch_bounds__(256) void df_update_kernel(double *__restrict__ L, const double *__restrict__ W, int n,
+                                                        int p) {
+  __shared__ double xr[FB][FBP], xi[FB][FBP], yr[FB][FBP], yi[FB][FBP];
+  const int tid = threadIdx.x, p0 = p * FB;
+  const int ib = p + 1 + blockIdx.y, kb = PANEL ? p : p + 1 + (int)blockIdx.z;
+  if (kb > ib) return;
+  double *Lk = L + 2 * (size_t)blockIdx.x * n * n;
+  const double *Y = PANEL ? W + 2 * (size_t)blockIdx.x * n * n : Lk;
+  for (int e = tid; e < FB * FB; e += 256) {
+    const int r = e / FB, c = e % FB;
+    const int ri = ib * FB + r, rk = kb * FB + r;
+    const double2 x = ri < n ? *reinterpret_cast<const double2 *>(Lk + 2 * ((size_t)ri * n + p0 + c))
+                             : make_double2(0.0, 0.0);
+    const double2 y = rk < n ? *reinterpret_cast<const double2 *>(Y + 2 * ((size_t)rk * n + p0 + c))
+                             : make_double2(0.0, 0.0);
+    xr[r][c] = x.x;
+    xi[r][c] = x.y;
+    yr[r][c] = y.x;
+    yi[r][c] = y.y;
+  }
+  __syncthreads();
+  df_d4 cre[4], cim[4];
+  df_xyh(xr, xi, yr, yi, cre, cim);
+  const int lane = tid & 63, wave = tid >> 6, li = lane & 15, lg = lane >> 4;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = ib * FB + 16 * wave + lg + 4 * v, q = kb * FB + 16 * c + li;
+      if (r >= n || q >= n || q > r) continue;
+      double2 *o = reinterpret_cast<double2 *>(Lk + 2 * ((size_t)r * n + q));
+      if (PANEL) {
+        *o = make_double2(cre[c][v], cim[c][v]);
+      } else {
+        const double2 old = *o;
+        *o = make_double2(old.x - cre[c][v], q == r ? 0.0 : old.y - cim[c][v]);
+      }
+    }
+}
+
+// W = L^{-1} below the diagonal blocks, a strip of 16 columns (of block j) per
+// workgroup: W_i = -W_ii sum_{j <= k < i} L_ik W_k for i = j + 1, ...  The wave's
+// operands come straight from memory (its 16 rows of L are its own, the strip's
+// rows are 256 contiguous bytes); only the sum crosses LDS, from the result
+// layout to the operand layout.
+__global__ __launch_bounds__(256, 1) void df_inverse_kernel(const double *__restrict__ L, double *W, int n) {
+  __shared__ double tr[FB][17], ti[FB][17];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lg = lane >> 4;
+  const int c0 = blockIdx.y * 16, jb = c0 / FB, nblk = (n + FB - 1) / FB;
+  const double2 *Lk = reinterpret_cast<const double2 *>(L) + (size_t)blockIdx.x * n * n;
+  double2 *Wk = reinterpret_cast<double2 *>(W) + (size_t)blockIdx.x * n * n;
+  const int col = c0 + li;
+  const double2 zero = make_double2(0.0, 0.0);
+  for (int ib = jb + 1; ib < nblk; ++ib) {
+    const int row = ib * FB + 16 * wave + li;
+    df_d4 sr = {0.0, 0.0, 0.0, 0.0}, si = sr;
+    for (int kb = jb; kb < ib; ++kb) {
+      double2 a[FB / 4], b[FB / 4];
+#pragma unroll
+      for (int ks = 0; ks < FB / 4; ++ks) {
+        const int t = kb * FB + 4 * ks + lg;  // kb < ib: inside the matrix
+        a[ks] = row < n ? Lk[(size_t)row * n + t] : zero;
+        b[ks] = col < n ? Wk[(size_t)t * n + col] : zero;
+      }
+#pragma unroll
+      for (int ks = 0; ks < FB / 4; ++ks) {
+        sr = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks].x, b[ks].x, sr, 0, 0, 0);
+        sr = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[ks].y, b[ks].y, sr, 0, 0, 0);
+        si = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks].x, b[ks].y, si, 0, 0, 0);
+        si = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks].y, b[ks].x, si, 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      tr[16 * wave + lg + 4 * v][li] = sr[v];
+      ti[16 * wave + lg + 4 * v][li] = si[v];
+    }
+    __syncthreads();
+    df_d4 dr = {0.0, 0.0, 0.0, 0.0}, di = dr;
+#pragma unroll 4
+    for (int ks = 0; ks < FB / 4; ++ks) {
+      const int t = 4 * ks + lg, tc = ib * FB + t;
+      const double2 a = (row < n && tc < n) ? Wk[(size_t)row * n + tc] : zero;
+      const double b_r = tr[t][li], b_i = ti[t][li];
+      dr = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.x, b_r, dr, 0, 0, 0);
+      dr = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b_i, dr, 0, 0, 0);
+      di = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.x, b_i, di, 0, 0, 0);
+      di = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b_r, di, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = ib * FB + 16 * wave + lg + 4 * v;
+      if (r < n && col < n) Wk[(size_t)r * n + col] = make_double2(dr[v], di[v]);
+    }
+    __threadfence_block();
+    __syncthreads();  // the strip's new rows are read by every wave in the next step
   }
 }
 
 hipError_t launch_df_factor(const double *J, double *L, double *W, int *bad, int nk, int n, hipStream_t stream) {
   if (nk == 0 || n == 0) return hipSuccess;
-  hipLaunchKernelGGL(chol_kernel, dim3((unsigned)nk), dim3(kCholThreads), 0, stream, J, L, n, bad);
-  hipLaunchKernelGGL(trinv_kernel, dim3((unsigned)((n + 255) / 256), (unsigned)nk), dim3(256), 0, stream, L, W, n);
+  const int64_t total = (int64_t)nk * n * n;
+  const int64_t g = (total > nk ? total : nk) / 256 + 1;
+  const int nblk = (n + FB - 1) / FB;
+  if (g > 0x7fffffff || nblk > 65535) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL(df_init_kernel, dim3((unsigned)g), dim3(256), 0, stream, reinterpret_cast<const double2 *>(J),
+                     reinterpret_cast<double2 *>(L), reinterpret_cast<double2 *>(W), n, total, bad, nk);
+  for (int p = 0; p < nblk; ++p) {
+    hipLaunchKernelGGL(df_diag_kernel, dim3((unsigned)nk), dim3(256), 0, stream, J, L, W, n, p, bad);
+    const unsigned rest = (unsigned)(nblk - 1 - p);
+    if (rest == 0) break;
+    hipLaunchKernelGGL(df_update_kernel<true>, dim3((unsigned)nk, rest), dim3(256), 0, stream, L, W, n, p);
+    hipLaunchKernelGGL(df_update_kernel<false>, dim3((unsigned)nk, rest, rest), dim3(256), 0, stream, L, W, n, p);
+  }
+  if (nblk > 1)
+    hipLaunchKernelGGL(df_inverse_kernel, dim3((unsigned)nk, (unsigned)((nblk - 1) * (FB / 16))), dim3(256), 0, stream,
+                       L, W, n);
   return hipGetLastError();
 }
 
@@ -144,7 +274,6 @@ hipError_t launch_df_factor(const double *J, double *L, double *W, int *bad, int
 // waves as 4 (rows of 32) x 2 (columns of 64); 16 q per step staged in LDS,
 // the next step's loads in flight during the MFMAs.  Fragments (li = lane %
 // 16, lg = lane / 16): A[li][lg], B[lg][li]; result D[lg + 4 v][li].
-typedef double df_d4 __attribute__((ext_vector_type(4)));
 constexpr int DG_BM = 128, DG_BN = 128, DG_BK = 16, DG_NT = 512;
 
 template <bool CONJT>
