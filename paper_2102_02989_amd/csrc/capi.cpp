@@ -1422,8 +1422,7 @@ int Job::prepare(hipStream_t st, double mem_frac) {
           const int lP = hp.ax[tr.aux].l, la = hp.ao[pp.sa].l, lb = hp.ao[pp.sb].l;
           // one unit per lane: a wave takes 64 / ncbw images of a class at a time, so
           // a cell range narrower than that leaves lanes empty
-          if (sr_unit_class(lP, la, lb))
-            ncbw = std::max<int>(ncbw, (int)std::min<int64_t>(nk, 64 * (int64_t)nk / std::max<int64_t>(nimg_pair[tr.pair], 1)));
+          ncbw = std::max<int>(ncbw, (int)std::min<int64_t>(nk, 64 * (int64_t)nk / std::max<int64_t>(nimg_pair[tr.pair], 1)));
           ncbw = std::min(ncbw, sr_cells_per_wave(lP, la, lb));  // BvK cells per wave
           const int nranges = (nk + ncbw - 1) / ncbw;
           int nsl = (int)std::min<int64_t>(64, (want + nranges - 1) / nranges);

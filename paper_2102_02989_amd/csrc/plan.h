@@ -36,26 +36,23 @@ __host__ __device__ constexpr int ncart(int l) { return (l + 1) * (l + 2) / 2; }
 __host__ __device__ inline double pair_growth_c(double beta) { return sqrt(2.0 * beta); }
 __host__ __device__ constexpr int nherm(int l) { return (l + 1) * (l + 2) * (l + 3) / 6; }
 
-// Work layout of the short-range kernels, shared with the planner's work split.
-constexpr int kBlkCap = 1024;        // doubles of per-group Cartesian accumulators in LDS
-constexpr int kMaxCellsPerWave = 8;  // BvK cells (lane groups) per wave
-// cells per wave for which the Cartesian accumulators of a class fit in LDS
-__host__ __device__ constexpr int sr_max_cells(int nblk) {
-  return (kBlkCap / nblk) < 1 ? 1 : ((kBlkCap / nblk) > kMaxCellsPerWave ? kMaxCellsPerWave : kBlkCap / nblk);
-}
+// Work layout of the short-range kernel, shared with the planner's work split.
+constexpr int kMaxCellsPerWave = 8;  // BvK cells per wave
 // Aux Hermite orders tau that a shell of angular momentum lP expands into:
 // |tau| = lP, then |tau| = lP - 2 (single-centre coefficients keep the parity).
 __host__ __device__ constexpr int sr_ntau(int lP) { return ncart(lP) + (lP >= 2 ? ncart(lP - 2) : 0); }
-// Classes of the one-unit-per-lane kernel: a lane's sums over the aux Hermite
-// orders and the AO components stay in its registers (126 doubles are half of
-// a one-wave register file, the rest holds the Hermite integrals).
+// Classes whose sums over (tau, AO components) fit a lane's registers: 126
+// doubles are half of a one-wave register file, the Hermite integrals and their
+// recursion take the rest.  Above that ((d|dd): 252, (f|dp): 234, (f|dd): 468)
+// the sums are spread over lanes, one (cell, tau) each.
 constexpr int kUnitAccMax = 126;
 __host__ __device__ constexpr bool sr_unit_class(int lP, int la, int lb) {
   return sr_ntau(lP) * ncart(la) * ncart(lb) <= kUnitAccMax;
 }
 // most BvK cells of one wave
 inline int sr_cells_per_wave(int lP, int la, int lb) {
-  return sr_unit_class(lP, la, lb) ? kMaxCellsPerWave : sr_max_cells(ncart(lP) * ncart(la) * ncart(lb));
+  const int wide = 64 / sr_ntau(lP);
+  return sr_unit_class(lP, la, lb) || wide > kMaxCellsPerWave ? kMaxCellsPerWave : wide;
 }
 // AO pair class of (l_a, l_b), l_a >= l_b: 0 ss, 1 ps, 2 pp, 3 ds, 4 dp, 5 dd
 inline int pair_class(int la, int lb) {

@@ -8,29 +8,26 @@
 // Terms are grouped by Born-von Karman cells (Eq. M14): c1 = c(m) and
 // c2 = c(m + n').
 //
-// Two kernels, chosen per angular class by sr_unit_class (plan.h):
-// sr3c_unit_kernel, a lane per (pair image, cell) unit, and sr3c_kernel for the
-// classes whose sums do not fit a lane's registers ((d|dd), (f|dp), (f|dd)).
-//
-// sr3c_kernel's lane layout: the 64 lanes form groups of gs lanes, group g
-// owning BvK cell c1 = g.  For each pair image n' (taken in the pair list order, which is
-// sorted by the BvK class of n', so the target (c1, c2) changes only with the
-// class) the wave
-//   1. enumerates the lattice vectors m of each cell inside the screening
-//      radius and keeps those passing the per-term window test of the
-//      Supplementary Material (R_c <= R_c^cut of Eq. S14 and R12 <= R12^cut(R_c)
-//      of Eqs. S23-S25, most diffuse primitives as 1s functions); survivors are
-//      compacted into per-group LDS lists with ballots (deterministic order);
-//   2. for every primitive pair (and aux primitive) sums the Hermite Coulomb
-//      integrals R_tuv of the erfc operator over the group's list (the only
-//      m-dependent factor of the McMurchie-Davidson expression), reduces them
-//      over the group's lanes in lane order (transposed through LDS), and
-//      contracts them with the aux (E^c) and pair (E^ab) Hermite coefficients;
-//   3. adds the Cartesian block into an LDS accumulator per group, flushed to
-//      X[c1][c2][P][mu][nu] (or to the wave's partial block when the images
-//      of the item are split over several waves) when the class of n' changes.
-// Every X element (and every partial element) is owned by one wave and one
-// group, so results are deterministic without atomics; split items are summed
+// Lane layout: a lane takes one unit, that is a pair image n', a BvK cell c1 and a
+// share of the lattice vectors m of that cell; a wave takes rows of ncb cells,
+// a row being (a share of) an image, and images in the pair list order (sorted
+// by the BvK class of n', so the target (c1, c2) changes only with the class).
+//   1. 64 images at a time are put to the per-term window test of the
+//      Supplementary Material (Eqs. S23-S25, most diffuse primitives as 1s
+//      functions); the kept ones queue up in LDS, and a batch of them gets the
+//      wave's rows in proportion to its lattice vectors;
+//   2. every lane lists the lattice vectors of its unit inside the screening
+//      radius (R_c <= R_c^cut of Eq. S14 and R12 <= R12^cut(R_c));
+//   3. for every primitive triple it sums the Hermite Coulomb integrals R_tuv of
+//      the erfc operator over its list (the only m-dependent factor of the
+//      McMurchie-Davidson expression) and contracts them with the pair's E^ab,
+//      in its registers (or, for the classes with the most components, through
+//      LDS with a lane per (cell, aux Hermite order));
+//   4. when the class of n' ends, the lanes are added in row order, the aux
+//      coefficients E^c applied, and X[c1][c2][P][mu][nu] (or the wave's partial
+//      block when the images of the item are split over several waves) stored.
+// Every X element (and every partial element) is owned by one wave and stored
+// once, so results are deterministic without atomics; split items are summed
 // by sr_reduce_kernel in slice order.
 #include <hip/hip_runtime.h>
 
@@ -41,10 +38,8 @@
 
 namespace rsgdf {
 
-constexpr int kCandCap = 1536;    // lattice-vector candidates held in LDS per wave
 constexpr int kSRWinCap = 256;    // screening windows held in LDS
-constexpr int kTripCap = 40;         // primitive triples whose constants are held in LDS
-constexpr int kTripC = 9;            // constants per primitive triple
+constexpr int kTripC = 9;         // constants per primitive triple
 
 // Constants of a primitive triple (AO a, AO b, aux c) that do not depend on
 // the pair image: t[0] 1/p, t[1] g_b/p (P = A + t[1] (B - A)), t[2] g_a g_b/p
@@ -83,34 +78,6 @@ __device__ __forceinline__ void triple_consts(double ga, double gb, double gc, d
 }
 
 
-// (t,u,v) of Hermite index h (inverse of hidx)
-__device__ __forceinline__ void herm_decode(int h, int &t, int &u, int &v) {
-  int s = 0;
-  while (nherm(s) <= h) ++s;
-  const int rem = h - (s > 0 ? nherm(s - 1) : 0);
-  int r = 0;
-  while ((r + 1) * (r + 2) / 2 <= rem) ++r;
-  v = rem - r * (r + 1) / 2;
-  u = r - v;
-  t = s - r;
-}
-
-// Cartesian powers of component i of angular momentum l
-__device__ __forceinline__ void cart_decode(int l, int i, int &x, int &y, int &z) {
-  int n = 0;
-  for (int lx = l; lx >= 0; --lx)
-    for (int ly = l - lx; ly >= 0; --ly) {
-      if (n == i) {
-        x = lx;
-        y = ly;
-        z = l - lx - ly;
-        return;
-      }
-      ++n;
-    }
-  x = y = z = 0;
-}
-
 __device__ __forceinline__ int pack3(int a, int b, int c) {
   return ((a + 512) & 1023) | (((b + 512) & 1023) << 10) | (((c + 512) & 1023) << 20);
 }
@@ -118,619 +85,6 @@ __device__ __forceinline__ void unpack3(int v, int &a, int &b, int &c) {
   a = (v & 1023) - 512;
   b = ((v >> 10) & 1023) - 512;
   c = ((v >> 20) & 1023) - 512;
-}
-
-// waves per SIMD the class's register need allows (the image loop keeps the
-// nherm(L) running sums and an nherm(L-1) recursion scratch live).  L = 4
-// runs two waves with some spilling (its LDS allows six workgroups per CU):
-// 2% faster on the 8-atom 2x2x2 workload than one wave.
-__host__ __device__ constexpr int sr_waves(int L) { return L >= 5 ? 1 : 2; }
-
-template <int LP, int LA, int LB>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sr_waves(LP + LA + LB))))
-void sr3c_kernel(const SRParams *__restrict__ prms, const SRWork *__restrict__ works, long long *__restrict__ counts,
-                 const int w0, const int) {
-  constexpr int NCP = ncart(LP), NCA = ncart(LA), NCB = ncart(LB);
-  constexpr int NBLK = NCP * NCA * NCB;
-  constexpr int LAB = LA + LB, L = LAB + LP;
-  constexpr int NH = nherm(L);
-  constexpr int NHAB = nherm(LAB);
-  constexpr int EA = (LA + 1) * (LB + 1) * (LAB + 1);
-  constexpr int BLK = NBLK * sr_max_cells(NBLK);
-  __shared__ float s_nf[kSRWinCap];
-  __shared__ __attribute__((aligned(16))) double s_boys[kBoysIntervals * (kBoysPolyDeg + 2)];
-  __shared__ int s_cand[kCandCap];
-  __shared__ double s_blk[BLK];
-  // contraction of all lane groups at once: W[g][ic][h] from the group sums
-  // R[g][h'] through a table of Hermite indices (NH marks an invalid aux
-  // order and reads the zero slot), then the components from W
-  constexpr int CH = 7;                    // Hermite entries per step of the group reduction (an odd
-                                           // row stride: the 64 lanes' rows start in distinct LDS banks)
-  constexpr int KX = LP / 2;               // aux Hermite orders tau = (c & 1) + 2k, k <= KX
-  constexpr int NK = (KX + 1) * (KX + 1) * (KX + 1);
-  constexpr int NW = NCP * NHAB;           // W entries per group
-  constexpr int MG = sr_max_cells(NBLK);   // groups per wave
-  // The reduction scratch (lane x entry) and the W table of the contraction
-  // share one buffer: within a primitive triple the reduction ends with a
-  // barrier before W is written, and the comps pass ends with one before the
-  // next triple's reduction writes its scratch.  (The classes with L >= 6
-  // stay under 40 KB of LDS this way: four one-wave workgroups per CU.)
-  constexpr int NTW = (64 * CH > MG * NW) ? 64 * CH : MG * NW;
-  __shared__ double s_TW[NTW];
-  double *const s_T = s_TW;
-  double *const s_W = s_TW;
-  __shared__ double s_R[MG * (NH + 1)];    // group sums (tetrahedral order) + a zero slot
-  __shared__ int s_wtab[NW];               // W entry (ic, h): cx | cy << 2 | cz << 4
-  __shared__ short s_widx[NW * NK];        // Hermite index of h + (tau nu phi), or NH
-  __shared__ int s_ctab[NBLK];             // component: ic | (ax,bx) << 8 | (ay,by) << 16 | (az,bz) << 24
-  __shared__ double s_E[3 * EA];
-  __shared__ double s_EP[(LP + 1) * (LP + 1)];
-  __shared__ double s_tc[kTripCap * kTripC];
-
-  const int lane = threadIdx.x;
-  const SRWork wk = works[w0 + blockIdx.x];
-  const SRParams &prm = prms[wk.cell];
-  const int S = wk.nslice;
-  const int slice = wk.slice;
-  const Triplet tr = prm.trip[wk.trip];
-  const Shell shP = prm.ax[tr.aux];
-  const Pair pr = prm.pairs[tr.pair];
-  const Shell shA = prm.ao[pr.sa];
-  const Shell shB = prm.ao[pr.sb];
-  const Lattice &lat = prm.lat;
-  const int nk = lat.nk;
-  const double omega = prm.omega, eps = prm.eps, dR = prm.dR;
-  const double fourpi_vol = 4.0 * kPi / lat.vol;
-
-  // ---- per-item tables in LDS: Boys polynomials of order L, screening windows
-  for (int i = lane; i < kBoysIntervals * (kBoysPolyDeg + 1); i += 64)
-    s_boys[(i / (kBoysPolyDeg + 1)) * (kBoysPolyDeg + 2) + i % (kBoysPolyDeg + 1)] = prm.boys[L * kBoysIntervals * (kBoysPolyDeg + 1) + i];
-  for (int i = lane; i < kBoysIntervals; i += 64) s_boys[i * (kBoysPolyDeg + 2) + kBoysPolyDeg + 1] = 0.0;
-  const int nta = shA.nprim, ntb = shB.nprim, ntcp = shP.nprim;
-  const int ntrip_p = nta * ntb * ntcp;
-  const bool tc_lds = ntrip_p <= kTripCap;
-  if (tc_lds)
-    for (int t = lane; t < ntrip_p; t += 64) {
-      const int kc = t % ntcp, kab = t / ntcp, kb = kab % ntb, ka = kab / ntb;
-      triple_consts<LP>(prm.ao_exp[shA.pptr + ka], prm.ao_exp[shB.pptr + kb], prm.ax_exp[shP.pptr + kc],
-                        prm.ao_coef[shA.pptr + ka], prm.ao_coef[shB.pptr + kb], prm.ax_coef[shP.pptr + kc],
-                        prm.ao_c1s[shA.pptr + ka], prm.ao_c1s[shB.pptr + kb], prm.ax_c1s[shP.pptr + kc], prm.omega, prm.acut,
-                        s_tc + t * kTripC);
-    }
-  const double pd = shA.a_d + shB.a_d;
-  const double beta = shA.a_d * shB.a_d / pd;
-  const double eta1 = sqrt(shP.a_d * pd / (shP.a_d + pd));
-  const double eta2 = 1.0 / sqrt(1.0 / (eta1 * eta1) + 1.0 / (omega * omega));
-  const int W = tr.nwin;
-  const double rc_cut = tr.rc_cut;
-  {
-    const double pref = tr.amp * fourpi_vol / (2.0 * beta);
-    for (int w = lane; w < W; w += 64) {
-      const double R = w * dR;
-      const double N = (R > prm.ncell_r0) ? fourpi_vol * 2.0 * (R + dR) * (R + dR) * dR : prm.ncell_nf;
-      const double f = (R < 1e-12) ? 2.0 * (eta1 - eta2) * 0.564189583547756286948079451561 /* 1/sqrt(pi) */
-                                   : (erf(eta1 * R) - erf(eta2 * R)) / R;
-      s_nf[w] = (float)(pref * N * f);
-    }
-  }
-  for (int i = lane; i < BLK; i += 64) s_blk[i] = 0.0;
-  for (int i = lane; i < MG * (NH + 1); i += 64) s_R[i] = 0.0;
-  for (int idx = lane; idx < NW; idx += 64) {
-    const int ic = idx / NHAB, h = idx % NHAB;
-    int t, u, v, cx, cy, cz;
-    herm_decode(h, t, u, v);
-    cart_decode(LP, ic, cx, cy, cz);
-    s_wtab[idx] = cx | (cy << 2) | (cz << 4);
-    for (int k = 0; k < NK; ++k) {
-      const int kx = k / ((KX + 1) * (KX + 1)), ky = (k / (KX + 1)) % (KX + 1), kz = k % (KX + 1);
-      const int tx = (cx & 1) + 2 * kx, ty = (cy & 1) + 2 * ky, tz = (cz & 1) + 2 * kz;
-      s_widx[idx * NK + k] = (tx <= cx && ty <= cy && tz <= cz) ? (short)hidx(t + tx, u + ty, v + tz) : (short)NH;
-    }
-  }
-  for (int comp = lane; comp < NBLK; comp += 64) {
-    const int ic = comp / (NCA * NCB), ia = (comp / NCB) % NCA, ib = comp % NCB;
-    int ax_, ay_, az_, bx_, by_, bz_;
-    cart_decode(LA, ia, ax_, ay_, az_);
-    cart_decode(LB, ib, bx_, by_, bz_);
-    s_ctab[comp] = ic | ((ax_ * (LB + 1) + bx_) << 8) | ((ay_ * (LB + 1) + by_) << 16) | ((az_ * (LB + 1) + bz_) << 24);
-  }
-  __syncthreads();
-  const bool logging = prm.logmag != nullptr;
-  const int64_t cbase = (prm.mask || logging) ? prm.cand_off[wk.trip] : 0;
-  const double xstar = 1.0 / sqrt(2.0 * beta);
-  const double gmax = xstar * exp(-0.5);
-  const double wgrow = pair_growth_c(beta);
-  const double inv_dR = 1.0 / dR;
-
-  const double Ax = shA.x, Ay = shA.y, Az = shA.z;
-  const double Cx = shP.x, Cy = shP.y, Cz = shP.z;
-  const double *a = lat.a;
-  const double *b = lat.b;
-  const double inv2pi = 1.0 / (2.0 * kPi);
-  double bn[3];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) bn[d] = sqrt(b[3 * d] * b[3 * d] + b[3 * d + 1] * b[3 * d + 1] + b[3 * d + 2] * b[3 * d + 2]);
-
-  // group layout: ncb groups of gs = floor(64 / ncb) lanes (any count, so that
-  // 5, 6 or 7 cells per wave keep 60-63 lanes busy), group gl owns BvK cell cb0 + gl
-  const int ncbw = wk.ncb;
-  const int gs = 64 / ncbw;
-  const int lig = lane % gs;
-  const int gl = lane / gs;
-  const unsigned long long gmask_lo = (gs == 64) ? ~0ull : ((1ull << gs) - 1ull);
-  const bool blk_in_lds = NBLK * ncbw <= BLK;
-  double *const part = (wk.part >= 0) ? prm.part + wk.part : nullptr;
-
-  const size_t xplane = (size_t)prm.naux_b * prm.nao * prm.nao;
-  const int pf0 = shP.foff - prm.aux_f0;
-  long long n_terms = 0, n_contr = 0, n_shell = 0;
-
-  const int nimg_all = prm.cls_off[pr.cls_off + nk];
-
-  {
-    const int c1 = wk.cb0 + gl;  // this group's BvK cell
-    const int ngrp = ncbw;
-    const bool grp_on = gl < ngrp;
-    int i1[3] = {0, 0, 0};
-    if (grp_on) {
-      i1[0] = c1 / (lat.n[1] * lat.n[2]);
-      i1[1] = (c1 / lat.n[2]) % lat.n[1];
-      i1[2] = c1 % lat.n[2];
-    }
-    const int capb = kCandCap / ngrp;
-    int cur_cls = -1;  // class of the n' whose sums sit in the LDS accumulator
-
-    // flush the LDS accumulator of class cls into X
-    auto flush = [&](int cls) {
-      if (!blk_in_lds || cls < 0) return;
-      if (grp_on) {
-        // c2 = c1 + cls (component-wise mod n)
-        const int dc0 = cls / (lat.n[1] * lat.n[2]), dc1 = (cls / lat.n[2]) % lat.n[1], dc2 = cls % lat.n[2];
-        const int c2 = (((i1[0] + dc0) % lat.n[0]) * lat.n[1] + (i1[1] + dc1) % lat.n[1]) * lat.n[2] +
-                       (i1[2] + dc2) % lat.n[2];
-        double *X12 = prm.X + (size_t)(c1 * nk + c2) * xplane;
-        double *X21 = prm.X + (size_t)(c2 * nk + c1) * xplane;
-        double *pb = part ? part + ((size_t)gl * nk + c2) * NBLK : nullptr;
-        for (int comp = lig; comp < NBLK; comp += gs) {
-          const double v = s_blk[gl * NBLK + comp];
-          s_blk[gl * NBLK + comp] = 0.0;
-          if (v == 0.0) continue;
-          if (pb) {
-            pb[comp] += v;
-            continue;
-          }
-          const int ic = comp / (NCA * NCB), ia = (comp / NCB) % NCA, ib = comp % NCB;
-          const size_t rowP = (size_t)(pf0 + ic) * prm.nao;
-          double *x12 = X12 + (rowP + shA.foff + ia) * prm.nao + shB.foff + ib;
-          double *x21 = X21 + (rowP + shB.foff + ib) * prm.nao + shA.foff + ia;
-          // Outside logging runs each element is flushed once: the class's
-          // images are contiguous in the list, the item's cell range is its
-          // own, and the transposed block lies in the other shell's rows.  X
-          // starts at zero, so a store replaces the read-modify-write.
-          if (logging) {
-            *x12 += v;
-            if (!pr.diag) *x21 += v;
-          } else {
-            *x12 = v;
-            if (!pr.diag) *x21 = v;
-          }
-        }
-      }
-    };
-
-    int cls = 0;
-    for (int ii = slice; ii < nimg_all; ii += S) {
-      // class of this image (the list is grouped by class)
-      while (prm.cls_off[pr.cls_off + cls + 1] <= ii) ++cls;
-      if (ii - prm.cls_off[pr.cls_off + cls] >= prm.nsr[pr.nsr_off + cls]) continue;  // beyond the SR radius
-      if (prm.mask && !prm.mask[cbase + ii]) continue;  // dropped by the learned screen
-      const double *nv = prm.img + 3 * (size_t)(pr.img_off + ii);
-      const double Bx = shB.x + nv[0], By = shB.y + nv[1], Bz = shB.z + nv[2];
-      const double ABx = Ax - Bx, ABy = Ay - By, ABz = Az - Bz;
-      const double r12sq = ABx * ABx + ABy * ABy + ABz * ABz;
-      const double R12 = sqrt(r12sq);
-      // window test of Eqs. S23-S24: keep R_c window w iff R12 <= R12cut(w)
-      double thr;
-      if (R12 <= pr.R12min) thr = 0.0;
-      else {
-        double gx = (R12 <= xstar) ? gmax : R12 * exp(-beta * r12sq);
-        if constexpr (LA + LB > 0) {  // angular growth of the pair factor
-          const double gr = fma(wgrow, R12, 1.0);
-          double gp = gr;
-#pragma unroll
-          for (int i = 1; i < LA + LB; ++i) gp *= gr;
-          gx *= gp;
-        }
-        thr = eps / gx;
-      }
-      int wmax = -1;
-      for (int w = 0; w < W; ++w)
-        if (s_nf[w] >= thr) wmax = w;
-      if (wmax < 0) continue;
-      if (cls != cur_cls) {
-        flush(cur_cls);
-        cur_cls = cls;
-      }
-      const double rmax = fmin((wmax + 1) * dR, rc_cut);
-      const double rmax2 = rmax * rmax;
-      // diffuse pair centre relative to the aux centre
-      const double Pdx = (shA.a_d * Ax + shB.a_d * Bx) / pd, Pdy = (shA.a_d * Ay + shB.a_d * By) / pd,
-                   Pdz = (shA.a_d * Az + shB.a_d * Bz) / pd;
-      const double X0x = Pdx - Cx, X0y = Pdy - Cy, X0z = Pdz - Cz;
-      // box of lattice coordinates M_d = i1_d + n_d j_d around -X0
-      int lo0, lo1, lo2, dim0, dim1, dim2;
-      {
-        const double f0 = -(b[0] * X0x + b[1] * X0y + b[2] * X0z) * inv2pi;
-        const double f1 = -(b[3] * X0x + b[4] * X0y + b[5] * X0z) * inv2pi;
-        const double f2 = -(b[6] * X0x + b[7] * X0y + b[8] * X0z) * inv2pi;
-        const double sp0 = rmax * bn[0] * inv2pi, sp1 = rmax * bn[1] * inv2pi, sp2 = rmax * bn[2] * inv2pi;
-        lo0 = (int)ceil((f0 - sp0 - i1[0]) / lat.n[0]);
-        lo1 = (int)ceil((f1 - sp1 - i1[1]) / lat.n[1]);
-        lo2 = (int)ceil((f2 - sp2 - i1[2]) / lat.n[2]);
-        dim0 = max(0, (int)floor((f0 + sp0 - i1[0]) / lat.n[0]) - lo0 + 1);
-        dim1 = max(0, (int)floor((f1 + sp1 - i1[1]) / lat.n[1]) - lo1 + 1);
-        dim2 = max(0, (int)floor((f2 + sp2 - i1[2]) / lat.n[2]) - lo2 + 1);
-      }
-      const int nbox = grp_on ? dim0 * dim1 * dim2 : 0;
-      // chunks of gs candidates; the wave loops to the largest group box
-      int nchunk = (nbox + gs - 1) / gs;
-      for (int off = 32; off >= 1; off >>= 1) nchunk = max(nchunk, __shfl_xor(nchunk, off, 64));
-
-      int pass = 0;
-      for (;;) {
-        // ---- enumerate and compact (this pass keeps candidates [pass*capb, (pass+1)*capb))
-        const int base = pass * capb;
-        int cnt = 0;
-        for (int ch = 0; ch < nchunk; ++ch) {
-          const int q = ch * gs + lig;
-          bool valid = false;
-          int M0 = 0, M1 = 0, M2 = 0;
-          if (q < nbox) {
-            const int j2 = q % dim2, j1 = (q / dim2) % dim1, j0 = q / (dim1 * dim2);
-            M0 = i1[0] + lat.n[0] * (lo0 + j0);
-            M1 = i1[1] + lat.n[1] * (lo1 + j1);
-            M2 = i1[2] + lat.n[2] * (lo2 + j2);
-            const double mx = X0x + M0 * a[0] + M1 * a[3] + M2 * a[6];
-            const double my = X0y + M0 * a[1] + M1 * a[4] + M2 * a[7];
-            const double mz = X0z + M0 * a[2] + M1 * a[5] + M2 * a[8];
-            const double rc2 = mx * mx + my * my + mz * mz;
-            if (rc2 <= rmax2) {
-              const double rc = sqrt(rc2);
-              const int w = (int)(rc * inv_dR);
-              valid = (rc <= rc_cut) && (w < W) && (s_nf[w] >= thr);
-            }
-          }
-          const unsigned long long bal = __ballot(valid);
-          const unsigned long long gb = (bal >> (gl * gs)) & gmask_lo;
-          const int pos = cnt + __popcll(gb & ((1ull << lig) - 1ull));
-          if (valid && pos >= base && pos < base + capb) s_cand[gl * capb + pos - base] = pack3(M0, M1, M2);
-          cnt += __popcll(gb);
-        }
-        const int total = cnt;
-        const int navail = min(max(total - base, 0), capb);
-        if (pass == 0 && lig == 0 && grp_on) n_shell += total;
-        // groups (bit gl * gs) holding lattice vectors in this pass; empty ones
-        // contribute nothing and skip their contraction
-        const unsigned long long gnz = __ballot(grp_on && lig == 0 && navail > 0);
-        __syncthreads();
-
-        // ---- primitive triples: image-summed Hermite integrals, then contraction
-        const double nm = 4.18879020478639098 * rmax2 * rmax / lat.vol + 1.0;
-        for (int tt = 0; tt < (gnz ? ntrip_p : 0); ++tt) {
-          double tcl[kTripC];
-          if (tc_lds) {
-#pragma unroll
-            for (int q = 0; q < kTripC; ++q) tcl[q] = s_tc[tt * kTripC + q];
-          } else {
-            const int kc = tt % ntcp, kab = tt / ntcp, kb = kab % ntb, ka = kab / ntb;
-            triple_consts<LP>(prm.ao_exp[shA.pptr + ka], prm.ao_exp[shB.pptr + kb], prm.ax_exp[shP.pptr + kc],
-                              prm.ao_coef[shA.pptr + ka], prm.ao_coef[shB.pptr + kb], prm.ax_coef[shP.pptr + kc],
-                              prm.ao_c1s[shA.pptr + ka], prm.ao_c1s[shB.pptr + kb], prm.ax_c1s[shP.pptr + kc],
-                              omega, prm.acut, tcl);
-          }
-          const double oop = tcl[0];
-          const double Kab = exp(-tcl[2] * r12sq);
-          // primitive screen: image-summed 1s estimate for this n' far below
-          // the target precision
-          if (tcl[7] * Kab * nm < 1e-4 * eps) continue;
-          const double Px = Ax + tcl[1] * (Bx - Ax), Py = Ay + tcl[1] * (By - Ay), Pz = Az + tcl[1] * (Bz - Az);
-          // offset of this primitive pair's centre from the aux centre at m = 0
-          const double dPx = Px - Pdx + X0x, dPy = Py - Pdy + X0y, dPz = Pz - Pdz + X0z;
-          {
-              const double rho = tcl[3];
-              const double th2 = tcl[4];
-              const double th = tcl[5];
-              const double m2rho = -2.0 * rho;
-              double Rb[NH];
-#pragma unroll
-              for (int i = 0; i < NH; ++i) Rb[i] = 0.0;
-              for (int e = lig; e < navail; e += gs) {
-                int M0, M1, M2;
-                unpack3(s_cand[gl * capb + e], M0, M1, M2);
-                const double X = dPx + M0 * a[0] + M1 * a[3] + M2 * a[6];
-                const double Y = dPy + M0 * a[1] + M1 * a[4] + M2 * a[7];
-                const double Z = dPz + M0 * a[2] + M1 * a[5] + M2 * a[8];
-                const double T = rho * (X * X + Y * Y + Z * Z);
-                double g[L + 1];
-                gvals_sr<L>(T, th2, th, s_boys, g);
-                double f = 1.0;
-#pragma unroll
-                for (int n = 1; n <= L; ++n) {
-                  f *= m2rho;
-                  g[n] *= f;
-                }
-                hermite_R_acc<L>(X, Y, Z, g, Rb);
-                ++n_terms;
-              }
-              // group reduction, transposed through LDS in chunks of CH entries:
-              // each entry of a group is summed by one lane over the group's gs
-              // lanes in lane order (deterministic), into s_R[group][h]
-#pragma unroll
-              for (int c0 = 0; c0 < NH; c0 += CH) {
-#pragma unroll
-                for (int j = 0; j < CH; ++j)
-                  if (c0 + j < NH) s_T[lane * CH + j] = Rb[c0 + j];
-                __syncthreads();
-                if (grp_on) {
-                  for (int j = lig; j < CH && c0 + j < NH; j += gs) {
-                    // reads issued eight at a time (gs >= 8); the sum keeps lane order
-                    const double *col = s_T + gl * gs * CH + j;
-                    double acc = 0.0;
-                    int r = 0;
-                    for (; r + 8 <= gs; r += 8) {
-                      double v[8];
-#pragma unroll
-                      for (int q = 0; q < 8; ++q) v[q] = col[(r + q) * CH];
-#pragma unroll
-                      for (int q = 0; q < 8; ++q) acc += v[q];
-                    }
-                    for (; r < gs; ++r) acc += col[r * CH];
-                    s_R[gl * (NH + 1) + c0 + j] = acc;
-                  }
-                }
-                __syncthreads();
-              }
-              // ---- contraction with the Hermite expansion coefficients: one
-              // group at a time, its sums in the LDS cube, output components
-              // spread over the 64 lanes; every loop bound is compile-time
-              if (lane < 3) {
-                double E1[LA + 1][LB + 1][LAB + 1];
-                const double PAd = (lane == 0) ? Px - Ax : (lane == 1 ? Py - Ay : Pz - Az);
-                const double PBd = (lane == 0) ? Px - Bx : (lane == 1 ? Py - By : Pz - Bz);
-                hermite_E<LA, LB>(PAd, PBd, 0.5 * oop, E1);
-#pragma unroll
-                for (int i = 0; i <= LA; ++i)
-#pragma unroll
-                  for (int j = 0; j <= LB; ++j)
-#pragma unroll
-                    for (int t = 0; t <= LAB; ++t) s_E[lane * EA + (i * (LB + 1) + j) * (LAB + 1) + t] = E1[i][j][t];
-              } else if (lane == 3) {
-                double E2[LP + 1][LP + 1];
-                hermite_E1<LP>(tcl[8], E2);
-#pragma unroll
-                for (int i = 0; i <= LP; ++i)
-#pragma unroll
-                  for (int t = 0; t <= LP; ++t) s_EP[i * (LP + 1) + t] = E2[i][t];
-              }
-              const double coef = tcl[6] * Kab;
-              __syncthreads();  // E coefficients and group sums visible to every lane
-              // W[g][ic][h] = sum_{tau nu phi} E^c_{cx,tau} E^c_{cy,nu} E^c_{cz,phi} R[g][h + (tau nu phi)]
-              if constexpr (L >= 5) {
-              // L >= 5 (one wave per SIMD, registers to spare in the AGPRs): a lane
-              // holds one entry's aux factors and Hermite indices and runs over the
-              // groups of its lane set (64 / NW sets when NW < 64); the lighter
-              // classes spill if they hold them, so their lanes take (group, entry)
-              // pairs in turn
-              constexpr int RW = NW >= 64 ? 1 : 64 / NW;
-              for (int cb = lane; cb < NW * RW; cb += 64) {
-                const int idx = cb % NW, gset = cb / NW;
-                const int w = s_wtab[idx];
-                const int cx = w & 3, cy = (w >> 2) & 3, cz = (w >> 4) & 3;
-                double ex[KX + 1], ey[KX + 1], ez[KX + 1];
-#pragma unroll
-                for (int k = 0; k <= KX; ++k) {
-                  const int tx = (cx & 1) + 2 * k, ty = (cy & 1) + 2 * k, tz = (cz & 1) + 2 * k;
-                  ex[k] = (tx <= cx) ? s_EP[cx * (LP + 1) + min(tx, LP)] : 0.0;
-                  ey[k] = (ty <= cy) ? s_EP[cy * (LP + 1) + min(ty, LP)] : 0.0;
-                  ez[k] = (tz <= cz) ? s_EP[cz * (LP + 1) + min(tz, LP)] : 0.0;
-                }
-                const short *wip = s_widx + idx * NK;
-                int wi[NK];
-#pragma unroll
-                for (int k = 0; k < NK; ++k) wi[k] = wip[k];
-                for (int g = gset; g < ngrp; g += RW) {
-                  if (!((gnz >> (g * gs)) & 1ull)) continue;
-                  const double *rg = s_R + g * (NH + 1);
-                  // every group sum this entry needs, read before the first multiply
-                  double rv[NK];
-#pragma unroll
-                  for (int k = 0; k < NK; ++k) rv[k] = rg[wi[k]];
-                  double sw = 0.0;
-#pragma unroll
-                  for (int kx = 0; kx <= KX; ++kx)
-#pragma unroll
-                    for (int ky = 0; ky <= KX; ++ky) {
-                      double sz = 0.0;
-#pragma unroll
-                      for (int kz = 0; kz <= KX; ++kz) sz += ez[kz] * rv[(kx * (KX + 1) + ky) * (KX + 1) + kz];
-                      sw += ex[kx] * ey[ky] * sz;
-                    }
-                  s_W[g * NW + idx] = sw;
-                }
-              }
-              } else {
-              for (int e = lane; e < ngrp * NW; e += 64) {
-                const int g = e / NW, idx = e - g * NW;
-                if (!((gnz >> (g * gs)) & 1ull)) continue;
-                const int w = s_wtab[idx];
-                const int cx = w & 3, cy = (w >> 2) & 3, cz = (w >> 4) & 3;
-                double ex[KX + 1], ey[KX + 1], ez[KX + 1];
-#pragma unroll
-                for (int k = 0; k <= KX; ++k) {
-                  const int tx = (cx & 1) + 2 * k, ty = (cy & 1) + 2 * k, tz = (cz & 1) + 2 * k;
-                  ex[k] = (tx <= cx) ? s_EP[cx * (LP + 1) + min(tx, LP)] : 0.0;
-                  ey[k] = (ty <= cy) ? s_EP[cy * (LP + 1) + min(ty, LP)] : 0.0;
-                  ez[k] = (tz <= cz) ? s_EP[cz * (LP + 1) + min(tz, LP)] : 0.0;
-                }
-                const double *rg = s_R + g * (NH + 1);
-                const short *wi = s_widx + idx * NK;
-                // every group sum this entry needs, read before the first multiply
-                double rv[NK];
-#pragma unroll
-                for (int k = 0; k < NK; ++k) rv[k] = rg[wi[k]];
-                double sw = 0.0;
-#pragma unroll
-                for (int kx = 0; kx <= KX; ++kx)
-#pragma unroll
-                  for (int ky = 0; ky <= KX; ++ky) {
-                    double sz = 0.0;
-#pragma unroll
-                    for (int kz = 0; kz <= KX; ++kz) sz += ez[kz] * rv[(kx * (KX + 1) + ky) * (KX + 1) + kz];
-                    sw += ex[kx] * ey[ky] * sz;
-                  }
-                s_W[g * NW + idx] = sw;
-              }
-              }
-              __syncthreads();
-              // component (ic, ia, ib) of group g = sum_{tuv} E^x_t E^y_u E^z_v W[g][ic][tuv]
-              if constexpr (L >= 5) {
-              // L >= 5: a lane holds one component's E rows in registers and runs
-              // over the groups of its lane set (64 / NBLK sets share the groups when
-              // NBLK < 64), so the rows are read once per component, not per group
-              constexpr int RS = NBLK >= 64 ? 1 : 64 / NBLK;
-              for (int cb = lane; cb < NBLK * RS; cb += 64) {
-                const int comp = cb % NBLK, gset = cb / NBLK;
-                const int c = s_ctab[comp];
-                const int ic = c & 0xff;
-                double ex[LAB + 1], ey[LAB + 1], ez[LAB + 1];
-#pragma unroll
-                for (int t = 0; t <= LAB; ++t) {
-                  ex[t] = s_E[0 * EA + ((c >> 8) & 0xff) * (LAB + 1) + t];
-                  ey[t] = s_E[1 * EA + ((c >> 16) & 0xff) * (LAB + 1) + t];
-                  ez[t] = s_E[2 * EA + ((c >> 24) & 0xff) * (LAB + 1) + t];
-                }
-                for (int g = gset; g < ngrp; g += RS) {
-                if (!((gnz >> (g * gs)) & 1ull)) continue;
-                const double *wr = s_W + g * NW + ic * NHAB;
-                double so = 0.0;
-#pragma unroll
-                for (int t = 0; t <= LAB; ++t) {
-                  double st = 0.0;
-#pragma unroll
-                  for (int u = 0; u <= LAB - t; ++u) {
-                    double su = 0.0;
-#pragma unroll
-                    for (int v = 0; v <= LAB - t - u; ++v) su += ez[v] * wr[hidx(t, u, v)];
-                    st += ey[u] * su;
-                  }
-                  so += ex[t] * st;
-                }
-                const double val = coef * so;
-                if (blk_in_lds) {
-                  s_blk[g * NBLK + comp] += val;
-                } else {
-                  const int cg = wk.cb0 + g;
-                  const int ig0 = cg / (lat.n[1] * lat.n[2]), ig1 = (cg / lat.n[2]) % lat.n[1], ig2 = cg % lat.n[2];
-                  const int dc0 = cls / (lat.n[1] * lat.n[2]), dc1 = (cls / lat.n[2]) % lat.n[1], dc2 = cls % lat.n[2];
-                  const int c2 = (((ig0 + dc0) % lat.n[0]) * lat.n[1] + (ig1 + dc1) % lat.n[1]) * lat.n[2] +
-                                 (ig2 + dc2) % lat.n[2];
-                  if (part) {
-                    part[((size_t)g * nk + c2) * NBLK + comp] += val;
-                  } else {
-                    const int ia = (comp / NCB) % NCA, ib = comp % NCB;
-                    const size_t rowP = (size_t)(pf0 + ic) * prm.nao;
-                    prm.X[(size_t)(cg * nk + c2) * xplane + (rowP + shA.foff + ia) * prm.nao + shB.foff + ib] += val;
-                    if (!pr.diag)
-                      prm.X[(size_t)(c2 * nk + cg) * xplane + (rowP + shB.foff + ib) * prm.nao + shA.foff + ia] += val;
-                  }
-                }
-                }
-              }
-              } else {
-              for (int e = lane; e < ngrp * NBLK; e += 64) {
-                const int g = e / NBLK, comp = e - g * NBLK;
-                if (!((gnz >> (g * gs)) & 1ull)) continue;
-                const int c = s_ctab[comp];
-                const int ic = c & 0xff;
-                const double *ex = s_E + 0 * EA + ((c >> 8) & 0xff) * (LAB + 1);
-                const double *ey = s_E + 1 * EA + ((c >> 16) & 0xff) * (LAB + 1);
-                const double *ez = s_E + 2 * EA + ((c >> 24) & 0xff) * (LAB + 1);
-                const double *wr = s_W + g * NW + ic * NHAB;
-                double so = 0.0;
-#pragma unroll
-                for (int t = 0; t <= LAB; ++t) {
-                  double st = 0.0;
-#pragma unroll
-                  for (int u = 0; u <= LAB - t; ++u) {
-                    double su = 0.0;
-#pragma unroll
-                    for (int v = 0; v <= LAB - t - u; ++v) su += ez[v] * wr[hidx(t, u, v)];
-                    st += ey[u] * su;
-                  }
-                  so += ex[t] * st;
-                }
-                const double val = coef * so;
-                if (blk_in_lds) {
-                  s_blk[g * NBLK + comp] += val;
-                } else {
-                  const int cg = wk.cb0 + g;
-                  const int ig0 = cg / (lat.n[1] * lat.n[2]), ig1 = (cg / lat.n[2]) % lat.n[1], ig2 = cg % lat.n[2];
-                  const int dc0 = cls / (lat.n[1] * lat.n[2]), dc1 = (cls / lat.n[2]) % lat.n[1], dc2 = cls % lat.n[2];
-                  const int c2 = (((ig0 + dc0) % lat.n[0]) * lat.n[1] + (ig1 + dc1) % lat.n[1]) * lat.n[2] +
-                                 (ig2 + dc2) % lat.n[2];
-                  if (part) {
-                    part[((size_t)g * nk + c2) * NBLK + comp] += val;
-                  } else {
-                    const int ia = (comp / NCB) % NCA, ib = comp % NCB;
-                    const size_t rowP = (size_t)(pf0 + ic) * prm.nao;
-                    prm.X[(size_t)(cg * nk + c2) * xplane + (rowP + shA.foff + ia) * prm.nao + shB.foff + ib] += val;
-                    if (!pr.diag)
-                      prm.X[(size_t)(c2 * nk + cg) * xplane + (rowP + shB.foff + ib) * prm.nao + shA.foff + ia] += val;
-                  }
-                }
-              }
-              }
-              __syncthreads();
-              if (lane == 0) n_contr += __popcll(gnz);  // (image, triple, cell group) contractions
-          }
-        }
-        // more candidates than one pass holds?
-        int more = (total > base + capb) ? 1 : 0;
-        for (int off = 32; off >= 1; off >>= 1) more = max(more, __shfl_xor(more, off, 64));
-        __syncthreads();
-        if (!more) break;
-        ++pass;
-      }
-      if (logging && blk_in_lds) {
-        // magnitude log: the accumulator holds only this pair image's block (it is
-        // flushed after every image in logging runs); max |block| per BvK cell c1,
-        // each (ii, c1) owned by one wave
-        if (grp_on && lig == 0) {
-          double mx = 0.0;
-          for (int comp = 0; comp < NBLK; ++comp) mx = fmax(mx, fabs(s_blk[gl * NBLK + comp]));
-          prm.logmag[(cbase + ii) * nk + c1] = (float)mx;
-        }
-        flush(cur_cls);
-        __syncthreads();
-      }
-    }
-    flush(cur_cls);
-    __syncthreads();
-  }
-
-  // ---- work counters (deterministic integer reduction), one slot per item
-  for (int off = 32; off >= 1; off >>= 1) {
-    n_terms += __shfl_xor(n_terms, off, 64);
-    n_contr += __shfl_xor(n_contr, off, 64);
-    n_shell += __shfl_xor(n_shell, off, 64);
-  }
-  if (lane == 0) {
-    long long *dst = counts + 4 * ((size_t)w0 + blockIdx.x);
-    dst[0] = n_terms;
-    dst[1] = n_contr;
-    dst[2] = n_shell;
-    dst[3] = 0;
-  }
 }
 
 // ---- one unit per lane ----------------------------------------------------------
@@ -778,6 +132,26 @@ constexpr int kUnitWaves = 4;   // waves per workgroup (they share the Boys tabl
 enum { uA = 0, uB = 3, uC = 6, uBeta = 9, uXstar, uGmax, uGrow, uR12min, uRc, uT1d, uRb, uSp = uRb + 9, uOn = uSp + 3,
        uNum = uOn + 3 };
 enum { nPa = 0, nPb, nPp, nTa, nTb, nTp, nFa, nFb, nFp, nDiag, nMesh, nNcb = nMesh + 3, nImg, nCoff, nNsr, nW, nNum };
+// the classes with more accumulators than a lane holds
+constexpr int kWideUnits = 16;  // units whose Hermite sums are in LDS at a time
+constexpr int kWideRows = 8;    // most rows (images) among them
+// offset of E^{ij}_t, t = 0 .. i + j, in a row of the nonzero coefficients (i, then j)
+__host__ __device__ constexpr int e_off(int LB, int i, int j) {
+  int o = 0;
+  for (int a = 0; a <= i; ++a)
+    for (int b = 0; b <= (a == i ? j - 1 : LB); ++b) o += a + b + 1;
+  return o;
+}
+// powers of Hermite index h (inverse of hidx)
+__host__ __device__ constexpr int herm_pow(int h, int d) {
+  int s = 0;
+  while (nherm(s) <= h) ++s;
+  const int rem = h - (s > 0 ? nherm(s - 1) : 0);
+  int r = 0;
+  while ((r + 1) * (r + 2) / 2 <= rem) ++r;
+  const int v = rem - r * (r + 1) / 2;
+  return d == 0 ? s - r : (d == 1 ? r - v : v);
+}
 constexpr int kUnitClsBits = 20, kUnitClsMask = (1 << kUnitClsBits) - 1;
 
 // LDS written by some lanes of the wave is read by others: program order of the
@@ -791,7 +165,8 @@ __device__ __forceinline__ void wave_sync() {
 // scratch, accumulators)
 __host__ __device__ constexpr int sr_unit_waves(int LP, int LA, int LB) {
   const int L = LP + LA + LB;
-  const int d = nherm(L) + (L > 0 ? nherm(L - 1) : 0) + sr_ntau(LP) * ncart(LA) * ncart(LB);
+  const int d = nherm(L) + (L > 0 ? nherm(L - 1) : 0) +
+                (sr_unit_class(LP, LA, LB) ? sr_ntau(LP) : 2) * ncart(LA) * ncart(LB);
   return d <= 30 ? 3 : (d <= 75 ? 2 : 1);
 }
 
@@ -817,6 +192,12 @@ __host__ __device__ constexpr int sr_unit_waves(int LP, int LA, int LB) {
 // double zeta 2x2x2, omega 0.5: 692 -> 238 ms; 4 atoms 3x3x3, omega 1.5: 646 ->
 // 167 ms; 3 atoms 1x3x2, omega 1: 247 -> 94 ms; 12 atoms single zeta 4x4x4,
 // omega 0.1: 274 -> 89 ms; 2 atoms at Gamma, omega 0.1: 1.51 -> 1.26 ms.
+//
+// The wide classes ((d|dd), (f|dp), (f|dd)) would need 234 to 468 accumulators a
+// lane.  Their sums cross LDS: 16 units at a time, whose R_tuv the lanes of
+// (cell, tau) gather at h + tau, each keeping its NAB components in registers.
+// With the cooperative kernel for these three the first three workloads above
+// were 238, 167 and 94 ms; they are 144, 109 and 58 ms.
 template <int LP, int LA, int LB>
 __global__ __launch_bounds__(64 * kUnitWaves) __attribute__((amdgpu_waves_per_eu(sr_unit_waves(LP, LA, LB))))
 void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restrict__ works,
@@ -826,6 +207,11 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
   constexpr int LAB = LA + LB, L = LAB + LP;
   constexpr int NH = nherm(L);
   constexpr int NT = sr_ntau(LP);
+  constexpr bool WIDE = !sr_unit_class(LP, LA, LB);
+  constexpr int NACC = WIDE ? NAB : NT * NAB;
+  constexpr int RS = NH | 1;                    // odd: the units' sums start in distinct banks
+  constexpr int NE = e_off(LB, LA, LB + 1);     // nonzero E coefficients per axis
+  constexpr int NHAB = nherm(LAB);
   constexpr int NBUF = kUnitCand * 32 > 64 * kUnitFl ? kUnitCand * 32 : 64 * kUnitFl;
   struct WaveLds {
     double buf[NBUF];  // candidate lists [entry][lane]; flush values [component][lane]
@@ -837,6 +223,8 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
     unsigned cnt[3 * 64];  // per lane: terms, contractions, lattice vectors
     double u[uNum];        // the item's constants, read where they are used: in
     int n[nNum];           // registers they would push the lanes' sums to scratch
+    double R[WIDE ? kWideUnits * RS : 1];         // wide classes: Hermite sums [unit][h]
+    double E[WIDE ? kWideRows * 3 * NE : 1];      // and the E^ab of their images [row][axis]
   };
   __shared__ double2 s_boys[(L > 0 ? kBoysFineTab : 8 * kBoysFine) / 2];
   __shared__ WaveLds s_wave[kUnitWaves];
@@ -925,9 +313,23 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
   }
   const int nimg_all = __builtin_amdgcn_readfirstlane(prm.cls_off[uni(nCoff) + nk]);
 
-  double acc[NT * NAB];
+  // wide classes: in the contraction the lanes are (part of the rows, cell, tau)
+  const int nct = ncb * NT, nsub = WIDE ? 64 / nct : 1;
+  const int sub2 = lane / nct, g2 = (lane - sub2 * nct) / NT, tau2 = lane - sub2 * nct - g2 * NT;
+  int hix[WIDE ? (NHAB + 1) / 2 : 1];  // R index of Hermite order h + tau, two per register
+  if constexpr (WIDE) {
+    const int tx = tau_pow(LP, tau2, 0), ty = tau_pow(LP, tau2, 1), tz = tau_pow(LP, tau2, 2);
+    static_for<0, (NHAB + 1) / 2>([&](auto I) {
+      constexpr int h0 = 2 * decltype(I)::v, h1 = h0 + 1 < NHAB ? h0 + 1 : h0;
+      constexpr int t0 = herm_pow(h0, 0), u0 = herm_pow(h0, 1), v0 = herm_pow(h0, 2);
+      constexpr int t1 = herm_pow(h1, 0), u1 = herm_pow(h1, 1), v1 = herm_pow(h1, 2);
+      hix[h0 / 2] = hidx(t0 + tx, u0 + ty, v0 + tz) | (hidx(t1 + tx, u1 + ty, v1 + tz) << 16);
+    });
+  }
+
+  double acc[NACC];
 #pragma unroll
-  for (int i = 0; i < NT * NAB; ++i) acc[i] = 0.0;
+  for (int i = 0; i < NACC; ++i) acc[i] = 0.0;
 
   // geometry of pair image ii: B + n' - A
   auto image_vec = [&](int ii, double &bx, double &by, double &bz) {
@@ -1015,7 +417,8 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
       const unsigned long long lim = nibmax >= 64 ? ~0ull : ((1ull << nibmax) - 1ull);
       ends = __ballot(in && (cj != cn || logging)) & lim;
       ended = ends != 0;
-      m = !ended ? nibmax : (open ? __ffsll((long long)ends) : 64 - __clzll((long long)ends));
+      // (the wide classes' accumulators are shared by the rows: one class at a time)
+      m = !ended ? nibmax : (open || WIDE ? __ffsll((long long)ends) : 64 - __clzll((long long)ends));
       if (m < 64) ends &= (1ull << m) - 1ull;
       const bool lastj = in && ((ends >> lane) & 1ull);
       if (lastj) s_runcls[__popcll(ends & ((1ull << lane) - 1ull))] = cj;
@@ -1149,6 +552,74 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
         wave_sync();  // (the constants below are read again, not kept over the loop)
         s_cnt[lane] += (unsigned)nt;
         s_cnt[64 + lane] += (unsigned)((nt > 0) & (share == 0));
+        if constexpr (WIDE) {
+          // A few rows at a time: their lanes put the Hermite sums and E^ab (with
+          // the prefactor in the x rows) into LDS, then lane (cell, tau) gathers
+          // R[h + tau] of every row of its part and adds its NAB components.
+          const unsigned long long bal = __ballot(nt > 0);
+          const int RP = min(max(kWideUnits / ncb, 1), kWideRows);
+          const double cK = tcl[6] * Kab, tb = tcl[1] - 1.0, oo2p = 0.5 * tcl[0], t1 = tcl[1];
+          double sc = 1.0;  // (1/2g)^{(lP + |tau|)/2} of the lane's tau
+#pragma unroll
+          for (int i = 0; i < LP; ++i) sc *= (i < LP - 1 || tau2 < NCP) ? tcl[8] : 1.0;
+          const unsigned long long cells = (1ull << ncb) - 1ull;
+          for (int r0 = 0; r0 < rows; r0 += RP) {
+            if (!((bal >> (r0 * ncb)) & ((r0 + RP) * ncb >= 64 ? ~0ull : ((1ull << (RP * ncb)) - 1ull)))) continue;
+            wave_sync();
+            if (row >= r0 && row < r0 + RP && lane_on) {
+              double *Ru = sl.R + ((row - r0) * ncb + gl) * RS;
+              static_for<0, NH>([&](auto I) { Ru[decltype(I)::v] = Rb[decltype(I)::v]; });
+              if (gl == 0) {
+                static_for<0, 3>([&](auto D) {
+                  constexpr int d = decltype(D)::v;
+                  const double ba = d == 0 ? BAx : (d == 1 ? BAy : BAz);
+                  double E1[LA + 1][LB + 1][LAB + 1];
+                  hermite_E<LA, LB>(t1 * ba, tb * ba, oo2p, E1);
+                  double *Ed = sl.E + ((row - r0) * 3 + d) * NE;
+                  static_for<0, (LA + 1) * (LB + 1)>([&](auto IJ) {
+                    constexpr int i = decltype(IJ)::v / (LB + 1), j = decltype(IJ)::v % (LB + 1);
+                    static_for<0, i + j + 1>([&](auto T) {
+                      constexpr int tt_ = decltype(T)::v;
+                      Ed[e_off(LB, i, j) + tt_] = d == 0 ? cK * E1[i][j][tt_] : E1[i][j][tt_];
+                    });
+                  });
+                });
+              }
+            }
+            wave_sync();
+            for (int rr = sub2; rr < RP && r0 + rr < rows; rr += nsub) {
+              if (sub2 >= nsub || !((bal >> ((r0 + rr) * ncb)) & cells)) continue;
+              const double *Ru = sl.R + (rr * ncb + g2) * RS;
+              const double *Ex = sl.E + rr * 3 * NE, *Ey = Ex + NE, *Ez = Ey + NE;
+              double r[NHAB];
+              static_for<0, NHAB>([&](auto I) {
+                constexpr int h_ = decltype(I)::v;
+                r[h_] = Ru[(h_ & 1) ? (hix[h_ / 2] >> 16) : (hix[h_ / 2] & 0xffff)];
+              });
+              static_for<0, NAB>([&](auto I) {
+                constexpr int i = decltype(I)::v, ia = i / NCB, ib = i % NCB;
+                constexpr int ax_ = crt_x(LA, ia), ay_ = crt_y(LA, ia), az_ = crt_z(LA, ia);
+                constexpr int bx_ = crt_x(LB, ib), by_ = crt_y(LB, ib), bz_ = crt_z(LB, ib);
+                double so = 0.0;
+                static_for<0, ax_ + bx_ + 1>([&](auto T) {
+                  constexpr int t_ = decltype(T)::v;
+                  double st = 0.0;
+                  static_for<0, ay_ + by_ + 1>([&](auto U) {
+                    constexpr int u_ = decltype(U)::v;
+                    double su = 0.0;
+                    static_for<0, az_ + bz_ + 1>([&](auto V) {
+                      constexpr int v_ = decltype(V)::v;
+                      su += Ez[e_off(LB, az_, bz_) + v_] * r[hidx(t_, u_, v_)];
+                    });
+                    st += Ey[e_off(LB, ay_, by_) + u_] * su;
+                  });
+                  so += Ex[e_off(LB, ax_, bx_) + t_] * st;
+                });
+                acc[i] += sc * so;
+              });
+            }
+          }
+        } else {
         // E^ab per axis from P - A = t1 (B - A), P - B = (t1 - 1)(B - A)
         double Ex[LA + 1][LB + 1][LAB + 1], Ey[LA + 1][LB + 1][LAB + 1], Ez[LA + 1][LB + 1][LAB + 1];
         const double tb = tcl[1] - 1.0, oo2p = 0.5 * tcl[0];
@@ -1182,6 +653,7 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
           });
           acc[i] += (tau < NCP ? ct : cl) * so;
         });
+        }
       }
       if (!__any(q < nbox)) break;
     }
@@ -1203,6 +675,50 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
       const size_t xplane = (size_t)prm.naux_b * nao * nao;
       double *const part = (wk.part >= 0) ? prm.part + wk.part : nullptr;
       wave_sync();
+      // one element of the block of cell g, class target c2
+      auto put = [&](int g, int c2, int comp, double v) {
+        if (logging) {
+          atomicMax(&s_mx[g], (unsigned long long)__double_as_longlong(fabs(v)));
+          return;
+        }
+        if (v == 0.0) return;
+        const int cc = wk.cb0 + g;
+        if (part) {
+          part[((size_t)g * nk + c2) * NBLK + comp] = v;
+          return;
+        }
+        const int ic = comp / NAB, ia = (comp / NCB) % NCA, ib = comp % NCB;
+        const size_t rowP = (size_t)(s_n[nFp] + ic) * nao;
+        const int fa = s_n[nFa] + ia, fb = s_n[nFb] + ib;
+        prm.X[(size_t)(cc * nk + c2) * xplane + (rowP + fa) * nao + fb] = v;
+        if (!s_n[nDiag]) prm.X[(size_t)(c2 * nk + cc) * xplane + (rowP + fb) * nao + fa] = v;
+      };
+      if constexpr (WIDE) {
+        constexpr int NFW = NAB < kUnitFl ? NAB : kUnitFl;
+        static_for<0, (NAB + NFW - 1) / NFW>([&](auto F0) {
+          constexpr int f0 = decltype(F0)::v * NFW;
+          static_for<0, NFW>([&](auto J) {
+            constexpr int j = decltype(J)::v;
+            if constexpr (f0 + j < NAB) s_buf[j * 64 + lane] = acc[f0 + j];
+          });
+          wave_sync();
+          for (int t = lane; t < ncb_f * NCP * NFW; t += 64) {
+            const int g = t / (NCP * NFW), ic = (t / NFW) % NCP, j = t % NFW;
+            if (f0 + j >= NAB) continue;
+            double v = 0.0;
+            for (int sb = 0; sb < nsub; ++sb) {
+              const double *col = s_buf + j * 64 + sb * nct + g * NT;
+              v += col[ic];
+              for (int d = 0; d < 3; ++d) {
+                const int c = tau_pow(LP, ic, d);
+                if (LP >= 2 && c >= 2) v += (c == 3 ? 3.0 : 1.0) * col[NCP + tau_low(LP, ic, d)];
+              }
+            }
+            put(g, s_c2[g], ic * NAB + f0 + j, v);
+          }
+          wave_sync();
+        });
+      } else
       static_for<0, (NBLK + NF - 1) / NF>([&](auto F0) {
         constexpr int f0 = decltype(F0)::v * NF;
         static_for<0, NF>([&](auto J) {
@@ -1226,28 +742,14 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
           double v = 0.0;
           for (int r = 0; r < rows; ++r)
             if (s_rowcls[r] == cls) v += s_buf[j * 64 + r * ncb + g];
-          if (logging) {
-            atomicMax(&s_mx[g], (unsigned long long)__double_as_longlong(fabs(v)));
-            continue;
-          }
-          if (v == 0.0) continue;
-          const int c2 = s_c2[kg], cc = wk.cb0 + g;
-          if (part) {
-            part[((size_t)g * nk + c2) * NBLK + comp] = v;
-            continue;
-          }
-          const int ic = comp / NAB, ia = (comp / NCB) % NCA, ib = comp % NCB;
-          const size_t rowP = (size_t)(s_n[nFp] + ic) * nao;
-          const int fa = s_n[nFa] + ia, fb = s_n[nFb] + ib;
-          prm.X[(size_t)(cc * nk + c2) * xplane + (rowP + fa) * nao + fb] = v;
-          if (!s_n[nDiag]) prm.X[(size_t)(c2 * nk + cc) * xplane + (rowP + fb) * nao + fa] = v;
+          put(g, s_c2[kg], comp, v);
         }
         wave_sync();
       });
       if (logging && lane < ncb)
         prm.logmag[(prm.cand_off[wk.trip] + s_qii[qh]) * nk + wk.cb0 + lane] = (float)__longlong_as_double((long long)s_mx[lane]);
 #pragma unroll
-      for (int i = 0; i < NT * NAB; ++i) acc[i] = 0.0;
+      for (int i = 0; i < NACC; ++i) acc[i] = 0.0;
       wave_sync();
     }
     open = !ended;
@@ -1311,18 +813,8 @@ hipError_t launch_sr_reduce(const SRParams &prm, const SRPartGroup *groups, int 
 
 typedef void (*sr_kernel_t)(const SRParams *, const SRWork *, long long *, const int, const int);
 
-// the kernel of a class and its waves per workgroup
-struct SREntry {
-  sr_kernel_t k;
-  int waves;
-};
-template <int LP, int LA, int LB>
-constexpr SREntry sr_entry() {
-  if constexpr (sr_unit_class(LP, LA, LB)) return {&sr3c_unit_kernel<LP, LA, LB>, kUnitWaves};
-  else return {&sr3c_kernel<LP, LA, LB>, 1};
-}
-#define RSGDF_SR_ENTRY(LP, LA, LB) sr_entry<LP, LA, LB>()
-static const SREntry kSRTable[4][6] = {
+#define RSGDF_SR_ENTRY(LP, LA, LB) &sr3c_unit_kernel<LP, LA, LB>
+static const sr_kernel_t kSRTable[4][6] = {
     {RSGDF_SR_ENTRY(0, 0, 0), RSGDF_SR_ENTRY(0, 1, 0), RSGDF_SR_ENTRY(0, 1, 1), RSGDF_SR_ENTRY(0, 2, 0),
      RSGDF_SR_ENTRY(0, 2, 1), RSGDF_SR_ENTRY(0, 2, 2)},
     {RSGDF_SR_ENTRY(1, 0, 0), RSGDF_SR_ENTRY(1, 1, 0), RSGDF_SR_ENTRY(1, 1, 1), RSGDF_SR_ENTRY(1, 2, 0),
@@ -1337,9 +829,8 @@ static const SREntry kSRTable[4][6] = {
 hipError_t launch_sr3c(int lP, int pc, const SRParams *prms, const SRWork *works, long long *counts, int w0,
                        int nwork, hipStream_t stream) {
   if (nwork <= 0) return hipSuccess;
-  const SREntry &e = kSRTable[lP][pc];
-  hipLaunchKernelGGL(e.k, dim3((unsigned)((nwork + e.waves - 1) / e.waves)), dim3(64 * e.waves), 0, stream, prms, works,
-                     counts, w0, nwork);
+  hipLaunchKernelGGL(kSRTable[lP][pc], dim3((unsigned)((nwork + kUnitWaves - 1) / kUnitWaves)), dim3(64 * kUnitWaves), 0,
+                     stream, prms, works, counts, w0, nwork);
   return hipGetLastError();
 }
 
