@@ -215,11 +215,12 @@ int rsgdf_df_solve(const int32_t kmesh[3], int64_t naux, int64_t ncol, const voi
  *   J_{mu nu}(k) = (1/Nk) sum_Q V^{kk}_{Q mu nu} c_Q.
  * The k1 = k2 blocks of V are built per group of aux shells (aux_group
  * shells per group, 0: groups sized to 10% of free device memory, at most
- * 8 GB), contracted and dropped; the second pass rebuilds them.  vj: device
- * complex128 [nk][nao][nao] (overwritten).  opt as for rsgdf_build_j3c_ex
+ * 8 GB), contracted and dropped; the second pass rebuilds all but the last.
+ * vj: device complex128 [nk][nao][nao] (overwritten).  opt as for
+ * rsgdf_build_j3c_ex
  * (parts must be all).  RSGDF_EINVAL if J^0 is numerically singular.
- * stats (optional): phase times and counts summed over both passes,
- * n_aux_batches = tiles built. */
+ * stats (optional): phase times and counts summed over the tiles built,
+ * n_aux_batches = their number. */
 int rsgdf_coulomb_direct(const rsgdf_cell *cell, const rsgdf_basis *basis, const rsgdf_basis *auxbasis,
                          const int32_t kmesh[3], double omega, double thresh, const rsgdf_options *opt,
                          int32_t aux_group, const void *dm, void *vj, void *stream, rsgdf_stats *stats);

@@ -593,20 +593,21 @@ std::vector<double> mesh_kvec(const Lattice &L) {
   return kv;
 }
 
-// G sets per folded k12 class c (Eq. M10): q = G + k_c, q != 0,
-// exp(-q^2/4w^2) >= g_thr, each sorted by |q|; qv [nq_tot][3], qoff [nk + 1]
-void make_qsets(const Lat &lt, const std::vector<double> &kvec, double omega, double g_thr, std::vector<double> &qv,
-                std::vector<int64_t> &qoff) {
+// q = G + k_c, q != 0, of every folded k12 class c that keep(q2) takes, each class
+// sorted by |q|, so that neighbouring lanes of the pair-transform kernel drop the
+// same primitive pairs (the e^{-q^2/4p} factor); qv [nq_tot][3], qoff [nk + 1].
+// The classes are independent: sorted on host threads where they are large.
+template <class Keep>
+void collect_q(const Lat &lt, const std::vector<double> &kvec, double qmax, Keep keep, std::vector<double> &qv,
+               std::vector<int64_t> &qoff) {
   const Lattice &L = lt.L;
-  const double q2max = -4.0 * omega * omega * std::log(g_thr);
-  qv.clear();
-  qoff.assign(1, 0);
-  for (int c = 0; c < L.nk; ++c) {
+  std::vector<std::vector<std::array<double, 4>>> cls(L.nk);  // (|q|^2, q)
+  auto one = [&](int64_t c) {
     const double *kc = &kvec[3 * c];
-    const double qm = std::sqrt(std::max(q2max, 0.0)) + std::sqrt(kc[0] * kc[0] + kc[1] * kc[1] + kc[2] * kc[2]);
+    const double qm = qmax + std::sqrt(kc[0] * kc[0] + kc[1] * kc[1] + kc[2] * kc[2]);
     int w[3];
     for (int d = 0; d < 3; ++d) w[d] = (int)std::ceil(qm * lt.an[d] / (2.0 * kPi)) + 1;
-    std::vector<std::array<double, 4>> qc;  // (|q|^2, q)
+    std::vector<std::array<double, 4>> &qc = cls[c];
     for (int i = -w[0]; i <= w[0]; ++i)
       for (int j = -w[1]; j <= w[1]; ++j)
         for (int k = -w[2]; k <= w[2]; ++k) {
@@ -615,50 +616,36 @@ void make_qsets(const Lat &lt, const std::vector<double> &kvec, double omega, do
             q[d] = i * L.b[d] + j * L.b[3 + d] + k * L.b[6 + d] + kc[d];
             q2 += q[d] * q[d];
           }
-          if (q2 < 1e-20) continue;
-          if (std::exp(-q2 / (4.0 * omega * omega)) < g_thr) continue;
+          if (q2 < 1e-20 || !keep(q2)) continue;
           qc.push_back({q2, q[0], q[1], q[2]});
         }
-    // by |q|, so that neighbouring lanes of the pair-transform kernel
-    // drop the same primitive pairs (the e^{-q^2/4p} factor)
     std::stable_sort(qc.begin(), qc.end(), [](const std::array<double, 4> &x, const std::array<double, 4> &y) {
       return x[0] < y[0];
     });
+  };
+  // points per class, about; threads from some 10^4 points on
+  const double npt = L.vol * qmax * qmax * qmax / 59.2;
+  parallel_for(L.nk, one, npt * L.nk > 2e4 ? 1 : L.nk);
+  qv.clear();
+  qoff.assign(1, 0);
+  for (const auto &qc : cls) {
     for (const auto &e : qc) qv.insert(qv.end(), e.begin() + 1, e.end());
     qoff.push_back((int64_t)qv.size() / 3);
   }
 }
 
-// q sets per folded k12 class c of a plain sphere: q = G + k_c, q != 0,
-// |q|^2 <= q2max, each sorted by |q| (the Eq. M15 part of the split)
+// G sets of the range-separated part (Eq. M10): exp(-q^2/4w^2) >= g_thr
+void make_qsets(const Lat &lt, const std::vector<double> &kvec, double omega, double g_thr, std::vector<double> &qv,
+                std::vector<int64_t> &qoff) {
+  const double q2max = -4.0 * omega * omega * std::log(g_thr);
+  collect_q(lt, kvec, std::sqrt(std::max(q2max, 0.0)),
+            [&](double q2) { return !(std::exp(-q2 / (4.0 * omega * omega)) < g_thr); }, qv, qoff);
+}
+
+// q sets of a plain sphere |q|^2 <= q2max (the Eq. M15 part of the split)
 void make_qsets_sphere(const Lat &lt, const std::vector<double> &kvec, double q2max, std::vector<double> &qv,
                        std::vector<int64_t> &qoff) {
-  const Lattice &L = lt.L;
-  qv.clear();
-  qoff.assign(1, 0);
-  for (int c = 0; c < L.nk; ++c) {
-    const double *kc = &kvec[3 * c];
-    const double qm = std::sqrt(q2max) + std::sqrt(kc[0] * kc[0] + kc[1] * kc[1] + kc[2] * kc[2]);
-    int w[3];
-    for (int d = 0; d < 3; ++d) w[d] = (int)std::ceil(qm * lt.an[d] / (2.0 * kPi)) + 1;
-    std::vector<std::array<double, 4>> qc;
-    for (int i = -w[0]; i <= w[0]; ++i)
-      for (int j = -w[1]; j <= w[1]; ++j)
-        for (int k = -w[2]; k <= w[2]; ++k) {
-          double q[3], q2 = 0.0;
-          for (int d = 0; d < 3; ++d) {
-            q[d] = i * L.b[d] + j * L.b[3 + d] + k * L.b[6 + d] + kc[d];
-            q2 += q[d] * q[d];
-          }
-          if (q2 < 1e-20 || q2 > q2max) continue;
-          qc.push_back({q2, q[0], q[1], q[2]});
-        }
-    std::stable_sort(qc.begin(), qc.end(), [](const std::array<double, 4> &x, const std::array<double, 4> &y) {
-      return x[0] < y[0];
-    });
-    for (const auto &e : qc) qv.insert(qv.end(), e.begin() + 1, e.end());
-    qoff.push_back((int64_t)qv.size() / 3);
-  }
+  collect_q(lt, kvec, std::sqrt(q2max), [&](double q2) { return !(q2 > q2max); }, qv, qoff);
 }
 
 // phase table kph[k][c] = e^{+i k.L_c} (complex, [nk][nk])
@@ -861,8 +848,12 @@ int build_plan(const rsgdf_cell *cell, const rsgdf_basis *bs, const rsgdf_basis 
       const double rc = solve_rc(K, eta2, thresh, sP.l + sA.l + sB.l);
       hp.rc_t[t] = rc;
       const int W = std::max(1, (int)std::ceil(rc / S.dR));
-      double nfmax = 0.0;
-      for (int w = 0; w < W; ++w) nfmax = std::max(nfmax, S.N(w * S.dR) * f_sr(w * S.dR, eta1, eta2));
+      // f falls with R (its derivative is h(eta2 R) - h(eta1 R) over R^2, h(x) =
+      // erf(x) - 2 x e^{-x^2} / sqrt(pi) increasing), so while N_cell is constant
+      // (R <= r0, usually every window) the first window has the largest product
+      double nfmax = S.N(0.0) * f_sr(0.0, eta1, eta2);
+      for (int w = std::max(1, (int)std::floor(S.r0 / S.dR)); w < W; ++w)
+        nfmax = std::max(nfmax, S.N(w * S.dR) * f_sr(w * S.dR, eta1, eta2));
       nfmax *= Aamp * 4.0 * kPi / L.vol / (2.0 * p.beta_d);
       r12t[t] = solve_r12_grow(nfmax, p.beta_d, thresh, sA.l + sB.l, pair_growth_c(p.beta_d));
     });
@@ -2708,30 +2699,32 @@ int rsgdf_build_j2c(const rsgdf_cell *cell, const rsgdf_basis *auxbasis, const i
   // below 1e-2 thresh (solve_rc, Eq. S14)
   std::vector<J2Pair> pairs;
   int cls_off[17] = {0};
+  std::vector<double> amp(nxs, 0.0);  // sum over the primitives, c^1s / a^{3/2}
+  for (int P = 0; P < nxs; ++P)
+    for (int i = 0; i < ax[P].nprim; ++i)
+      amp[P] += ax_c1s[ax[P].pptr + i] / std::pow(ax_exp[ax[P].pptr + i], 1.5);
   for (int lp = 0; lp <= 3; ++lp)
     for (int lq = 0; lq <= 3; ++lq) {
       for (int P = 0; P < nxs; ++P) {
         if (ax[P].l != lp) continue;
         for (int Q = 0; Q < nxs; ++Q) {
           if (ax[Q].l != lq) continue;
-          double K = 0.0;
-          for (int i = 0; i < ax[P].nprim; ++i)
-            for (int j = 0; j < ax[Q].nprim; ++j) {
-              const double a = ax_exp[ax[P].pptr + i], b = ax_exp[ax[Q].pptr + j];
-              K += kPi * kPi * kPi * ax_c1s[ax[P].pptr + i] * ax_c1s[ax[Q].pptr + j] / std::pow(a * b, 1.5);
-            }
-          const double a = ax[P].a_d, b = ax[Q].a_d;
-          const double e1 = std::sqrt(a * b / (a + b));
-          const double e2 = 1.0 / std::sqrt(1.0 / (e1 * e1) + 1.0 / (omega * omega));
           J2Pair jp{};
           jp.P = P;
           jp.Q = Q;
-          jp.rmax = solve_rc(K, e2, 1e-2 * thresh, lp + lq) + 1e-9;
           pairs.push_back(jp);
         }
       }
       cls_off[4 * lp + lq + 1] = (int)pairs.size();
     }
+  // the radii on host threads (0.7 us each: 18 ms for 160 shells on one)
+  parallel_for((int64_t)pairs.size(), [&](int64_t i) {
+    J2Pair &jp = pairs[i];
+    const Shell &sP = ax[jp.P], &sQ = ax[jp.Q];
+    const double e1 = std::sqrt(sP.a_d * sQ.a_d / (sP.a_d + sQ.a_d));
+    const double e2 = 1.0 / std::sqrt(1.0 / (e1 * e1) + 1.0 / (omega * omega));
+    jp.rmax = solve_rc(kPi * kPi * kPi * amp[jp.P] * amp[jp.Q], e2, 1e-2 * thresh, sP.l + sQ.l) + 1e-9;
+  }, 512);
   // S_P = int chi_P (all space) for the G = 0 term
   std::vector<double> SP(naux, 0.0);
   for (int s_ = 0; s_ < nxs; ++s_) {
@@ -3004,37 +2997,46 @@ int rsgdf_coulomb_direct(const rsgdf_cell *cell, const rsgdf_basis *basis, const
   }
   HIPCHK(d_V.alloc((size_t)nk * max_nf * ne * 16));
   HIPCHK(launch_zero(vj, (size_t)nk * ne * 16, st));
-  // one pass: rebuild the diagonal-k-pair tiles of every group; pass 0 forms
-  // rho, pass 1 accumulates J
+  // Pass 0 builds the diagonal-k-pair tile of every group and forms rho, pass 1
+  // accumulates J over the tiles in reverse, so that the last one, still in
+  // memory, is not built again (with one group, the usual case, nothing is:
+  // 6 atoms on a 2x2x2 mesh, with the planning below: 22 -> 11 ms).
+  const int ngrp = (int)gstart.size() - 1;
+  std::vector<int64_t> gf(ngrp + 1, 0);  // first function of each group
+  for (int g = 0; g < ngrp; ++g) {
+    gf[g + 1] = gf[g];
+    for (int s_ = gstart[g]; s_ < gstart[g + 1]; ++s_) gf[g + 1] += ncart_h(auxbasis->shell_l[s_]);
+  }
   for (int pass = 0; pass < 2; ++pass) {
-    int64_t f0 = 0;
-    for (size_t g = 0; g + 1 < gstart.size(); ++g) {
+    for (int i = 0; i < ngrp; ++i) {
+      const int g = pass == 0 ? i : ngrp - 1 - i;
       const int s0 = gstart[g], s1 = gstart[g + 1];
-      rsgdf_basis sub = *auxbasis;
-      sub.nshell = s1 - s0;
-      sub.shell_atom = auxbasis->shell_atom + s0;
-      sub.shell_l = auxbasis->shell_l + s0;
-      sub.shell_nprim = auxbasis->shell_nprim + s0;
-      sub.shell_ptr = auxbasis->shell_ptr + s0;
-      int64_t nf = 0;
-      for (int s_ = s0; s_ < s1; ++s_) nf += ncart_h(auxbasis->shell_l[s_]);
-      rsgdf_out o{};
-      o.data = d_V.p;
-      o.capacity_bytes = (int64_t)nk * nf * ne * 16;
-      o.on_device = 1;
-      o.stream = stream;
-      rsgdf_stats s2{};
-      o.stats = &s2;
-      int rc = build_impl(cell, basis, &sub, kmesh, omega, thresh, opt, &o, nullptr, true);
-      if (rc) return rc;
-      acc.t_plan_ms += s2.t_plan_ms;
-      acc.t_sr_ms += s2.t_sr_ms;
-      acc.t_fold_ms += s2.t_fold_ms;
-      acc.t_lr_ms += s2.t_lr_ms;
-      acc.t_lr_gemm_ms += s2.t_lr_gemm_ms;
-      acc.n_sr_terms += s2.n_sr_terms;
-      acc.n_lr_terms += s2.n_lr_terms;
-      acc.n_aux_batches += 1;
+      const int64_t f0 = gf[g], nf = gf[g + 1] - gf[g];
+      if (pass == 0 || i > 0) {
+        rsgdf_basis sub = *auxbasis;
+        sub.nshell = s1 - s0;
+        sub.shell_atom = auxbasis->shell_atom + s0;
+        sub.shell_l = auxbasis->shell_l + s0;
+        sub.shell_nprim = auxbasis->shell_nprim + s0;
+        sub.shell_ptr = auxbasis->shell_ptr + s0;
+        rsgdf_out o{};
+        o.data = d_V.p;
+        o.capacity_bytes = (int64_t)nk * nf * ne * 16;
+        o.on_device = 1;
+        o.stream = stream;
+        rsgdf_stats s2{};
+        o.stats = &s2;
+        int rc = build_impl(cell, basis, &sub, kmesh, omega, thresh, opt, &o, nullptr, true);
+        if (rc) return rc;
+        acc.t_plan_ms += s2.t_plan_ms;
+        acc.t_sr_ms += s2.t_sr_ms;
+        acc.t_fold_ms += s2.t_fold_ms;
+        acc.t_lr_ms += s2.t_lr_ms;
+        acc.t_lr_gemm_ms += s2.t_lr_gemm_ms;
+        acc.n_sr_terms += s2.n_sr_terms;
+        acc.n_lr_terms += s2.n_lr_terms;
+        acc.n_aux_batches += 1;
+      }
       if (pass == 0) {
         HIPCHK(launch_dm_contract(d_V.as<double>(), static_cast<const double *>(dm), nk, (int)nf, (int)nao,
                                   d_rho.as<double>() + 2 * f0, st));
@@ -3042,7 +3044,6 @@ int rsgdf_coulomb_direct(const rsgdf_cell *cell, const rsgdf_basis *basis, const
         HIPCHK(launch_vj_accum(d_V.as<double>(), d_c.as<double>() + 2 * f0, nk, (int)nf, ne, 1.0 / nk,
                                static_cast<double *>(vj), st));
       }
-      f0 += nf;
     }
     if (pass == 0) {  // c = (J^0)^{-1} rho = W^H (W rho)
       HIPCHK(launch_df_gemm(false, d_W.as<double>(), d_cls.as<int32_t>(), d_rho.as<double>(), d_y.as<double>(),
