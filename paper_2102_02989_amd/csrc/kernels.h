@@ -79,7 +79,7 @@ struct PairFTParams {
   long long *nterm;       // running count of transform evaluations
   double acut;            // primitive-pair selection (pmode) by exponents
   int32_t pmode;          // 0 every pair, 1 not both below acut, 2 both below acut
-  int32_t pad2;
+  int32_t nql;            // q per workgroup of the sliced form (set by the launcher)
 };
 
 // leading q columns of each k12 class (the smallest |q|) that the reduced-precision

@@ -123,14 +123,29 @@ __host__ __device__ constexpr int pairft_qpl(int la, int lb) {
   return la + lb == 0 ? 8 : (la + lb == 1 ? 4 : (la + lb <= 3 ? 2 : 1));
 }
 
-template <int LA, int LB>
-__device__ long long pairft_binned_one(const PairFTParams &pp, int ip, int c, int iq0) {
+constexpr int kPairFtWaves = 4;  // waves of a workgroup that share a pair's terms (sliced form)
+
+// BvK class -c
+__device__ __forceinline__ int neg_class(const PairFTParams &pp, int c) {
+  const int n0 = pp.kn[0], n1 = pp.kn[1], n2 = pp.kn[2];
+  const int i0 = c / (n1 * n2), i1 = (c / n2) % n1, i2 = c % n2;
+  return (((n0 - i0) % n0) * n1 + (n1 - i1) % n1) * n2 + (n2 - i2) % n2;
+}
+
+template <int LA, int LB, int QP, bool SLICED>
+__device__ __forceinline__ void pairft_binned_one(const PairFTParams &pp, int ip, int c, int yb) {
   constexpr int NCA = ncart(LA), NCB = ncart(LB);
   constexpr int LT = LA + LB;
-  constexpr int QP = pairft_qpl(LA, LB);
+  static_assert(!SLICED || QP == 1, "the sliced form has one q per lane");
   const Pair pr = pp.pairs[ip];
   const Shell s1 = pp.ao[pr.sa];
   const Shell s2 = pp.ao[pr.sb];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // SLICED: pp.nql q values (a power of two) per workgroup, the terms shared by
+  // the 64 / nql lane sets of its waves
+  const int nql = SLICED ? pp.nql : 64, nls = 64 / nql;
+  const int slice = SLICED ? wave * nls + lane / nql : 0, nslice = SLICED ? (int)(blockDim.x >> 6) * nls : 1;
+  const int iq0 = SLICED ? yb * nql + (lane & (nql - 1)) : yb * (64 * QP) + lane;
   // lane q values iq0 + 64 s, s < QP; idle slots of the last block follow a
   // valid q and write nothing
   bool live[QP];
@@ -186,6 +201,93 @@ __device__ long long pairft_binned_one(const PairFTParams &pp, int ip, int c, in
 #pragma unroll
   for (int s = 0; s < QP; ++s) nlive += live[s];
   const int beg = pp.cls_off[pr.cls_off + c], end = pp.cls_off[pr.cls_off + c + 1];
+  // one (primitive pair, image) term
+  auto add = [&](double ga, double gb, double oop, double er, double Rx, double Ry, double Rz, const double (&camp)[QP]) {
+    cnt += nlive;
+    // P - A = (gb/p) R, P - B = -(ga/p) R
+    const double wa = gb * oop, wb = -ga * oop;
+    const double Px = s1.x + wa * Rx, Py = s1.y + wa * Ry, Pz = s1.z + wa * Rz;
+    // F_d[i][j] = sum_t E_d[i][j][t] (-i q_d)^t, per q value of the lane
+    double Fr[QP][3][LA + 1][LB + 1], Fi[QP][3][LA + 1][LB + 1];
+    {
+      double E[LA + 1][LB + 1][LT + 1];
+      const double Rd[3] = {Rx, Ry, Rz};
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        hermite_E<LA, LB>(wa * Rd[d], wb * Rd[d], 0.5 * oop, E);
+#pragma unroll
+        for (int s = 0; s < QP; ++s)
+#pragma unroll
+          for (int i = 0; i <= LA; ++i)
+#pragma unroll
+            for (int j = 0; j <= LB; ++j) {
+              double re = 0.0, im = 0.0;
+#pragma unroll
+              for (int t = 0; t <= i + j; ++t) {
+                if ((t & 1) == 0) re += E[i][j][t] * qr[s][d][t];
+                else im += E[i][j][t] * qi[s][d][t];
+              }
+              Fr[s][d][i][j] = re;
+              Fi[s][d][i][j] = im;
+            }
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < QP; ++s) {
+      double sph, cph;
+      sincos(-(qx[s] * Px + qy[s] * Py + qz[s] * Pz), &sph, &cph);
+      const double amp = camp[s] * er;
+      const double cr = amp * cph, ci = amp * sph;
+      // fold the amplitude and phase into the x factor
+      double Gr[LA + 1][LB + 1], Gi[LA + 1][LB + 1];
+#pragma unroll
+      for (int i = 0; i <= LA; ++i)
+#pragma unroll
+        for (int j = 0; j <= LB; ++j) {
+          Gr[i][j] = cr * Fr[s][0][i][j] - ci * Fi[s][0][i][j];
+          Gi[i][j] = cr * Fi[s][0][i][j] + ci * Fr[s][0][i][j];
+        }
+#pragma unroll
+      for (int ia = 0; ia < NCA; ++ia)
+#pragma unroll
+        for (int ib = 0; ib < NCB; ++ib) {
+          const int ax_ = cart_lx(LA, ia), ay_ = cart_ly(LA, ia), az_ = cart_lz(LA, ia);
+          const int bx_ = cart_lx(LB, ib), by_ = cart_ly(LB, ib), bz_ = cart_lz(LB, ib);
+          const double xr = Gr[ax_][bx_] * Fr[s][1][ay_][by_] - Gi[ax_][bx_] * Fi[s][1][ay_][by_];
+          const double xi = Gr[ax_][bx_] * Fi[s][1][ay_][by_] + Gi[ax_][bx_] * Fr[s][1][ay_][by_];
+          accr[s][ia * NCB + ib] += xr * Fr[s][2][az_][bz_] - xi * Fi[s][2][az_][bz_];
+          acci[s][ia * NCB + ib] += xr * Fi[s][2][az_][bz_] + xi * Fr[s][2][az_][bz_];
+        }
+    }
+  };
+  const int nimg = end - beg;
+  if (SLICED && nimg < 2 * nslice) {
+    // few images: the lane sets take (image, primitive pair) terms in turn
+    const int npp = s1.nprim * s2.nprim;
+    const int64_t nt = (int64_t)nimg * npp;
+    for (int64_t t = slice; t < nt; t += nslice) {
+      const int im = (int)(t / npp), ab = (int)(t - (int64_t)im * npp);
+      const int ka = ab / s2.nprim, kb = ab - ka * s2.nprim;
+      const double ga = pp.ao_exp[s1.pptr + ka], gb = pp.ao_exp[s2.pptr + kb];
+      if (pp.pmode != 0) {
+        const bool dd = ga < pp.acut && gb < pp.acut;
+        if ((pp.pmode == 1) == dd) continue;
+      }
+      const double p = ga + gb, oop = 1.0 / p, beta = ga * gb * oop;
+      const double cc = pp.ao_coef[s1.pptr + ka] * pp.ao_coef[s2.pptr + kb] * kPi * oop * sqrt(kPi * oop);
+      const double cq = 1.0 + 0.5 * qnw * oop + sqrt(0.5 * LT * oop);
+      const double *nv = pp.img + 3 * ((size_t)pr.img_off + beg + im);
+      const double Rx = s2.x + nv[0] - s1.x, Ry = s2.y + nv[1] - s1.y, Rz = s2.z + nv[2] - s1.z;
+      const double r2 = Rx * Rx + Ry * Ry + Rz * Rz;
+      const double er = exp(-beta * r2);
+      double bnd = fabs(cc) * exp(-q2w * 0.25 * oop) * er;
+#pragma unroll
+      for (int i = 0; i < LT; ++i) bnd *= (cq + sqrt(r2));
+      if (bnd < cut) continue;
+      const double camp[QP] = {cc * exp(-q2[0] * 0.25 * oop)};
+      add(ga, gb, oop, er, Rx, Ry, Rz, camp);
+    }
+  } else {
   for (int ka = 0; ka < s1.nprim; ++ka)
     for (int kb = 0; kb < s2.nprim; ++kb) {
       const double ga = pp.ao_exp[s1.pptr + ka], gb = pp.ao_exp[s2.pptr + kb];
@@ -206,7 +308,7 @@ __device__ long long pairft_binned_one(const PairFTParams &pp, int ip, int c, in
       double camp[QP];
 #pragma unroll
       for (int s = 0; s < QP; ++s) camp[s] = cc * pre * exp(-q2[s] * 0.25 * oop);
-      for (int ii = beg; ii < end; ++ii) {
+      for (int ii = beg + slice; ii < end; ii += nslice) {
         const double *nv = pp.img + 3 * (size_t)(pr.img_off + ii);
         const double Bx = s2.x + nv[0], By = s2.y + nv[1], Bz = s2.z + nv[2];
         const double Rx = Bx - s1.x, Ry = By - s1.y, Rz = Bz - s1.z;
@@ -220,64 +322,40 @@ __device__ long long pairft_binned_one(const PairFTParams &pp, int ip, int c, in
           if (rr > rstar) break;
           continue;
         }
-        cnt += nlive;
-        // P - A = (gb/p) R, P - B = -(ga/p) R
-        const double wa = gb * oop, wb = -ga * oop;
-        const double Px = s1.x + wa * Rx, Py = s1.y + wa * Ry, Pz = s1.z + wa * Rz;
-        // F_d[i][j] = sum_t E_d[i][j][t] (-i q_d)^t, per q value of the lane
-        double Fr[QP][3][LA + 1][LB + 1], Fi[QP][3][LA + 1][LB + 1];
-        {
-          double E[LA + 1][LB + 1][LT + 1];
-          const double Rd[3] = {Rx, Ry, Rz};
-#pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            hermite_E<LA, LB>(wa * Rd[d], wb * Rd[d], 0.5 * oop, E);
-#pragma unroll
-            for (int s = 0; s < QP; ++s)
-#pragma unroll
-              for (int i = 0; i <= LA; ++i)
-#pragma unroll
-                for (int j = 0; j <= LB; ++j) {
-                  double re = 0.0, im = 0.0;
-#pragma unroll
-                  for (int t = 0; t <= i + j; ++t) {
-                    if ((t & 1) == 0) re += E[i][j][t] * qr[s][d][t];
-                    else im += E[i][j][t] * qi[s][d][t];
-                  }
-                  Fr[s][d][i][j] = re;
-                  Fi[s][d][i][j] = im;
-                }
-          }
-        }
-#pragma unroll
-        for (int s = 0; s < QP; ++s) {
-          double sph, cph;
-          sincos(-(qx[s] * Px + qy[s] * Py + qz[s] * Pz), &sph, &cph);
-          const double amp = camp[s] * er;
-          const double cr = amp * cph, ci = amp * sph;
-          // fold the amplitude and phase into the x factor
-          double Gr[LA + 1][LB + 1], Gi[LA + 1][LB + 1];
-#pragma unroll
-          for (int i = 0; i <= LA; ++i)
-#pragma unroll
-            for (int j = 0; j <= LB; ++j) {
-              Gr[i][j] = cr * Fr[s][0][i][j] - ci * Fi[s][0][i][j];
-              Gi[i][j] = cr * Fi[s][0][i][j] + ci * Fr[s][0][i][j];
-            }
-#pragma unroll
-          for (int ia = 0; ia < NCA; ++ia)
-#pragma unroll
-            for (int ib = 0; ib < NCB; ++ib) {
-              const int ax_ = cart_lx(LA, ia), ay_ = cart_ly(LA, ia), az_ = cart_lz(LA, ia);
-              const int bx_ = cart_lx(LB, ib), by_ = cart_ly(LB, ib), bz_ = cart_lz(LB, ib);
-              const double xr = Gr[ax_][bx_] * Fr[s][1][ay_][by_] - Gi[ax_][bx_] * Fi[s][1][ay_][by_];
-              const double xi = Gr[ax_][bx_] * Fi[s][1][ay_][by_] + Gi[ax_][bx_] * Fr[s][1][ay_][by_];
-              accr[s][ia * NCB + ib] += xr * Fr[s][2][az_][bz_] - xi * Fi[s][2][az_][bz_];
-              acci[s][ia * NCB + ib] += xr * Fi[s][2][az_][bz_] + xi * Fr[s][2][az_][bz_];
-            }
-        }
+        add(ga, gb, oop, er, Rx, Ry, Rz, camp);
       }
     }
+  }
+  if constexpr (SLICED) {
+    // sums over the lane sets (butterfly), then over the waves in order
+#pragma unroll
+    for (int i = 0; i < NCA * NCB; ++i)
+      for (int o = nql; o < 64; o <<= 1) {
+        accr[0][i] += __shfl_xor(accr[0][i], o, 64);
+        acci[0][i] += __shfl_xor(acci[0][i], o, 64);
+      }
+    if (blockDim.x > 64) {
+      __shared__ double2 s_red[kPairFtWaves][64];
+#pragma unroll
+      for (int i = 0; i < NCA * NCB; ++i) {
+        __syncthreads();
+        s_red[wave][lane] = make_double2(accr[0][i], acci[0][i]);
+        __syncthreads();
+        double re = s_red[0][lane].x, im = s_red[0][lane].y;
+        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
+          re += s_red[w][lane].x;
+          im += s_red[w][lane].y;
+        }
+        accr[0][i] = re;
+        acci[0][i] = im;
+      }
+    }
+    live[0] = live[0] && slice == 0;
+  }
+  // wave sum of the evaluation counts, one integer atomic per wave
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
+  if (lane == 0 && cnt) atomicAdd(reinterpret_cast<unsigned long long *>(pp.nterm), (unsigned long long)cnt);
   const int nao = pp.nao;
   const size_t nq = pp.nq;
   double *Ic = pp.B + 2 * ((size_t)c * nao * nao * nq);
@@ -286,7 +364,7 @@ __device__ long long pairft_binned_one(const PairFTParams &pp, int ip, int c, in
   if (!pr.diag) {
     const int n0 = pp.kn[0], n1 = pp.kn[1], n2 = pp.kn[2];
     const int i0 = c / (n1 * n2), i1 = (c / n2) % n1, i2 = c % n2;
-    cneg = (((n0 - i0) % n0) * n1 + (n1 - i1) % n1) * n2 + (n2 - i2) % n2;
+    cneg = neg_class(pp, c);
     // e^{+i k_cls.L_c} = e^{2 pi i sum_d j_d i_d / n_d}, reduced exactly in integers
     const int nt = n0 * n1 * n2;
     const int num = ((pp.kcls[0] * i0 % n0) * n1 * n2 + (pp.kcls[1] * i1 % n1) * n0 * n2 +
@@ -318,36 +396,72 @@ __device__ long long pairft_binned_one(const PairFTParams &pp, int ip, int c, in
         }
     }
   }
-  return cnt;
 }
 
-// grid: x = (pair of one angular group, class), y = blocks of 64 * pairft_qpl q;
+// grid: x = (pair of one angular group, class), y = blocks of 64 QP q (SLICED: nql);
 // one kernel per (l(sa), l(sb)) so that each runs at its own register count
-template <int LA, int LB>
-__global__ __launch_bounds__(64) void pairft_binned_kernel(const PairFTParams pp, int pbeg) {
+template <int LA, int LB, int QP, bool SLICED>
+__global__ __launch_bounds__(SLICED ? 64 * kPairFtWaves : 64) void pairft_binned_kernel(const PairFTParams pp,
+                                                                                         int pbeg) {
   const int ip = pp.plist[pbeg + (int)(blockIdx.x / pp.nk)], c = (int)(blockIdx.x % pp.nk);
-  const int iq0 = blockIdx.y * (64 * pairft_qpl(LA, LB)) + threadIdx.x;
-  long long cnt = pairft_binned_one<LA, LB>(pp, ip, c, iq0);
-  // wave sum of the evaluation counts, one integer atomic per wave
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-  if (threadIdx.x == 0 && cnt) atomicAdd(reinterpret_cast<unsigned long long *>(pp.nterm), (unsigned long long)cnt);
+  pairft_binned_one<LA, LB, QP, SLICED>(pp, ip, c, blockIdx.y);
+}
+
+// How a class's q are dealt out.  With at least 64 q the lanes are q, and each
+// takes as many of them as leave 8 waves per SIMD (a term's q-independent work
+// is done once per lane: at 2400 q per class and 45 to 78 pairs, 8 q per lane
+// left 2300 waves, the longest of which the launch waited for: 1x3x2 mesh, 52 ms
+// of pair transforms, 26 with this rule).  With fewer than 64 q (a Gamma or small-omega build has 6
+// to 30) the lanes beyond them would idle: they share the terms instead, and so
+// do four waves of a workgroup where the launch has few of them.
+struct PairFtShape {
+  int qp, nql, waves;  // q per lane; nql > 0: sliced form
+};
+PairFtShape pairft_shape(int64_t nx, int nq, int qpmax) {
+  const int64_t nw = nx * ((nq + 63) / 64);
+  if (nq < 64) {
+    int nql = 1;
+    while (nql < nq) nql *= 2;
+    return {1, nql, nw < 2048 ? kPairFtWaves : 1};
+  }
+  if (nw < 2048) return {1, 64, kPairFtWaves};
+  int qp = qpmax;
+  while (qp > 1 && nx * ((nq + 64 * qp - 1) / (64 * qp)) < 8192) qp /= 2;
+  return {qp, 0, 1};
+}
+
+template <int LA, int LB, int QP>
+void pairft_launch(const PairFTParams &pp, int pbeg, int64_t nx, const PairFtShape &sh, hipStream_t stream) {
+  if (sh.nql) {
+    PairFTParams ps = pp;
+    ps.nql = sh.nql;
+    hipLaunchKernelGGL((pairft_binned_kernel<LA, LB, 1, true>),
+                       dim3((unsigned)nx, (unsigned)((pp.nq + sh.nql - 1) / sh.nql)), dim3(64 * sh.waves), 0, stream, ps,
+                       pbeg);
+  } else if (sh.qp == QP) {
+    hipLaunchKernelGGL((pairft_binned_kernel<LA, LB, QP, false>),
+                       dim3((unsigned)nx, (unsigned)((pp.nq + 64 * QP - 1) / (64 * QP))), dim3(64), 0, stream, pp, pbeg);
+  } else if constexpr (QP > 1) {
+    pairft_launch<LA, LB, QP / 2>(pp, pbeg, nx, sh, stream);
+  }
 }
 
 hipError_t launch_pairft_binned(const PairFTParams &pp, hipStream_t stream) {
   if (pp.nq == 0 || pp.npair == 0) return hipSuccess;
-  typedef void (*K)(const PairFTParams, int);
-  const K ks[6] = {pairft_binned_kernel<2, 2>, pairft_binned_kernel<2, 1>, pairft_binned_kernel<2, 0>,
-                   pairft_binned_kernel<1, 1>, pairft_binned_kernel<1, 0>, pairft_binned_kernel<0, 0>};
   static const int la_of[6] = {2, 2, 2, 1, 1, 0}, lb_of[6] = {2, 1, 0, 1, 0, 0};
   for (int g = 0; g < 6; ++g) {
     const int64_t nx = (int64_t)(pp.pgrp[g + 1] - pp.pgrp[g]) * pp.nk;
     if (nx == 0) continue;
-    if (nx > 0x7fffffff) return hipErrorInvalidConfiguration;
-    const int64_t qb = 64 * pairft_qpl(la_of[g], lb_of[g]);
-    const int64_t ny = (pp.nq + qb - 1) / qb;
-    if (ny > 65535) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(ks[g], dim3((unsigned)nx, (unsigned)ny), dim3(64), 0, stream, pp, pp.pgrp[g]);
+    const PairFtShape sh = pairft_shape(nx, pp.nq, pairft_qpl(la_of[g], lb_of[g]));
+    if (nx > 0x7fffffff || (pp.nq + 63) / 64 > 65535) return hipErrorInvalidConfiguration;
+    switch (g) {
+      case 0: pairft_launch<2, 2, pairft_qpl(2, 2)>(pp, pp.pgrp[g], nx, sh, stream); break;
+      case 1: pairft_launch<2, 1, pairft_qpl(2, 1)>(pp, pp.pgrp[g], nx, sh, stream); break;
+      case 2: pairft_launch<2, 0, pairft_qpl(2, 0)>(pp, pp.pgrp[g], nx, sh, stream); break;
+      case 3: pairft_launch<1, 1, pairft_qpl(1, 1)>(pp, pp.pgrp[g], nx, sh, stream); break;
+      case 4: pairft_launch<1, 0, pairft_qpl(1, 0)>(pp, pp.pgrp[g], nx, sh, stream); break;
+      default: pairft_launch<0, 0, pairft_qpl(0, 0)>(pp, pp.pgrp[g], nx, sh, stream); break;
+    }
   }
   return hipGetLastError();
 }
