@@ -1627,7 +1627,7 @@ int Job::prepare(hipStream_t st, double mem_frac) {
     if (o.lr_precision == RSGDF_F16X3)  // whole 32-q blocks per chunk (the split format's unit)
       qchunk = std::max<int64_t>(kF16Blk * kF16Grp, qchunk / (kF16Blk * kF16Grp) * (kF16Blk * kF16Grp));
     HIPCHK(d_amax.alloc((size_t)qchunk * sizeof(double)));
-    HIPCHK(d_I.alloc((size_t)nk * qchunk * nao2 * 2 * sizeof(double)));
+    HIPCHK(d_I.alloc((size_t)nk * qchunk * (nao2 + nao) * sizeof(double)));  // rows mu >= nu
     HIPCHK(d_B.alloc((size_t)max_kpi * qchunk * nao2 * 2 * sizeof(double)));
     if (o.lr_precision != RSGDF_FP64)  // the FP64 innermost columns
       HIPCHK(d_Bhi.alloc((size_t)max_kpi * kLrNqHi * nao2 * 2 * sizeof(double)));
@@ -1637,18 +1637,21 @@ int Job::prepare(hipStream_t st, double mem_frac) {
     HIPCHK(d_nterm.alloc(sizeof(long long)));
     // k-pair lists and the phases e^{+i k2.L_c} of every class, as a table
     // [cell c][k-pair of the class] with the k-pairs contiguous and padded with
-    // zeros to whole passes of the k2-phase kernels
+    // zeros to whole passes of the k2-phase kernels, then e^{+i (k_cls - k2).L_c}
+    // (k_cls = k2 - k1, so the k is -k1) for the transposed blocks
     for (int c = 0; c < nk; ++c) {
       const int nkpi = (int)cls_kp[c].size(), kpad = kphase_kpad(std::max(nkpi, 1));
       for (int t : cls_kp[c]) kpl.push_back(t);
       kpl_off.push_back((int64_t)kpl.size());
       ph_off.push_back((int64_t)(phl.size() / 2));
-      for (int cell = 0; cell < nk; ++cell)
-        for (int k = 0; k < kpad; ++k) {
-          const int k2 = k < nkpi ? hp.kp2[cls_kp[c][k]] : -1;
-          phl.push_back(k2 >= 0 ? kph[2 * ((size_t)k2 * nk + cell)] : 0.0);
-          phl.push_back(k2 >= 0 ? kph[2 * ((size_t)k2 * nk + cell) + 1] : 0.0);
-        }
+      for (const bool trans : {false, true})
+        for (int cell = 0; cell < nk; ++cell)
+          for (int k = 0; k < kpad; ++k) {
+            const int kk = k >= nkpi ? -1 : (trans ? hp.kp1[cls_kp[c][k]] : hp.kp2[cls_kp[c][k]]);
+            const double sg = trans ? -1.0 : 1.0;
+            phl.push_back(kk >= 0 ? kph[2 * ((size_t)kk * nk + cell)] : 0.0);
+            phl.push_back(kk >= 0 ? sg * kph[2 * ((size_t)kk * nk + cell) + 1] : 0.0);
+          }
     }
     HIPCHK(d_ph.alloc(std::max<size_t>(phl.size(), 2) * sizeof(double)));
     if (!kpl.empty())

@@ -75,7 +75,7 @@ struct PairFTParams {
   int32_t kn[3];          // k-mesh (BvK class arithmetic)
   int32_t kcls[3];        // mesh coordinates j_d of k_cls
   double eps;             // skip terms whose weighted bound is below this
-  double *B;              // complex I[Nk BvK classes][nao][nao][nq]
+  double *B;              // complex I[Nk BvK classes][nao (nao + 1)/2 rows mu >= nu][nq]
   long long *nterm;       // running count of transform evaluations
   double acut;            // primitive-pair selection (pmode) by exponents
   int32_t pmode;          // 0 every pair, 1 not both below acut, 2 both below acut
@@ -136,10 +136,11 @@ hipError_t launch_lr_gemm_tiled(int mode, const LRGemmParams &gp, int q_lo, int 
 hipError_t launch_pairft_binned(const PairFTParams &pp, hipStream_t stream);
 hipError_t launch_amax(const double *A, int64_t lda, int naux, int nq, double *amax, hipStream_t stream);
 // k-pairs summed per pass of the k2-phase kernels for a class of nkpi k-pairs
-// (passes of equal width, at most 28; a class of up to 28 takes one pass of
-// exactly nkpi), and the k-pair stride of their phase table:
-// phase[c][k] = e^{+i k2(k).L_c}, zero for k >= nkpi
-constexpr int kKphKbMax = 28;
+// (passes of equal width, at most 18; a class of up to 18 takes one pass of
+// exactly nkpi), and the k-pair stride of their phase tables:
+// phase[c][k] = e^{+i k2(k).L_c}, zero for k >= nkpi, and after it
+// phase_t[c][k] = e^{+i (k_cls - k2(k)).L_c}
+constexpr int kKphKbMax = 18;
 __host__ __device__ inline int kphase_kb(int nkpi) {
   const int npass = (nkpi + kKphKbMax - 1) / kKphKbMax;
   return (nkpi + npass - 1) / npass;

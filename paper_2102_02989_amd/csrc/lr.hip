@@ -106,6 +106,10 @@ hipError_t launch_auxft(const AuxFTParams &ap, hipStream_t stream) {
 // same number times e^{+i q.n'}, and for q = G + k_cls with k_cls on the
 // k-mesh that phase is e^{+i k_cls.L_c} for every image of class c:
 //   I[-c][nu mu][q] = e^{+i k_cls.L_c} I[c][mu nu][q].
+// So I holds the components with mu >= nu alone, row mu (mu + 1)/2 + nu, and the
+// k2 phases read each row once for both: I is the largest array of the long
+// range (423 GB written and read per build of the 4-atom double-zeta cell on a
+// 3x3x3 mesh with both: 262 ms here and 131 there, 255 and 117 with these).
 //
 // A term (primitive pair, image) is skipped when max_P |A[P][q]| times the
 // bound  |c_a c_b| (pi/p)^{3/2} e^{-q^2/4p} e^{-beta r^2} (c_q + r)^{la+lb},
@@ -356,22 +360,23 @@ __device__ __forceinline__ void pairft_binned_one(const PairFTParams &pp, int ip
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
   if (lane == 0 && cnt) atomicAdd(reinterpret_cast<unsigned long long *>(pp.nterm), (unsigned long long)cnt);
-  const int nao = pp.nao;
-  const size_t nq = pp.nq;
-  double *Ic = pp.B + 2 * ((size_t)c * nao * nao * nq);
+  // the components with mu >= nu: the block itself (its lower half where a shell
+  // meets itself), or the transposed block of class -c
+  const size_t nq = pp.nq, nrow = (size_t)pp.nao * (pp.nao + 1) / 2;
+  const bool tr = s1.foff < s2.foff;
   double sp = 0.0, cp = 1.0;
-  int cneg = 0;
-  if (!pr.diag) {
+  int cd = c;
+  if (tr) {
     const int n0 = pp.kn[0], n1 = pp.kn[1], n2 = pp.kn[2];
     const int i0 = c / (n1 * n2), i1 = (c / n2) % n1, i2 = c % n2;
-    cneg = neg_class(pp, c);
+    cd = neg_class(pp, c);
     // e^{+i k_cls.L_c} = e^{2 pi i sum_d j_d i_d / n_d}, reduced exactly in integers
     const int nt = n0 * n1 * n2;
     const int num = ((pp.kcls[0] * i0 % n0) * n1 * n2 + (pp.kcls[1] * i1 % n1) * n0 * n2 +
                      (pp.kcls[2] * i2 % n2) * n0 * n1) % nt;
     sincospi(2.0 * num / nt, &sp, &cp);
   }
-  double *In = pp.B + 2 * ((size_t)cneg * nao * nao * nq);
+  double *Ic = pp.B + 2 * ((size_t)cd * nrow * nq);
 #pragma unroll
   for (int s = 0; s < QP; ++s) {
     if (!live[s]) continue;
@@ -380,21 +385,14 @@ __device__ __forceinline__ void pairft_binned_one(const PairFTParams &pp, int ip
     for (int ia = 0; ia < NCA; ++ia)
 #pragma unroll
       for (int ib = 0; ib < NCB; ++ib) {
-        const size_t o = ((size_t)(s1.foff + ia) * nao + s2.foff + ib) * nq + iq;
-        Ic[2 * o] = accr[s][ia * NCB + ib];
-        Ic[2 * o + 1] = acci[s][ia * NCB + ib];
+        const int fa = s1.foff + ia, fb = s2.foff + ib;
+        if (pr.diag && ib > ia) continue;
+        const size_t mu = tr ? fb : fa, nu = tr ? fa : fb;
+        const size_t o = (mu * (mu + 1) / 2 + nu) * nq + iq;
+        const double re = accr[s][ia * NCB + ib], im = acci[s][ia * NCB + ib];
+        Ic[2 * o] = tr ? cp * re - sp * im : re;
+        Ic[2 * o + 1] = tr ? cp * im + sp * re : im;
       }
-    if (!pr.diag) {
-#pragma unroll
-      for (int ia = 0; ia < NCA; ++ia)
-#pragma unroll
-        for (int ib = 0; ib < NCB; ++ib) {
-          const size_t o = ((size_t)(s2.foff + ib) * nao + s1.foff + ia) * nq + iq;
-          const double re = accr[s][ia * NCB + ib], im = acci[s][ia * NCB + ib];
-          In[2 * o] = cp * re - sp * im;
-          In[2 * o + 1] = cp * im + sp * re;
-        }
-    }
   }
 }
 
@@ -496,10 +494,14 @@ hipError_t launch_amax(const double *A, int64_t lda, int naux, int nq, double *a
   return hipGetLastError();
 }
 
-// B[kpi][mn][q] = sum_c phase[c][kpi] I[c][mn][q], phase = e^{+i k2.L_c}; one
-// thread per (mn, q) element.  The k-pairs of the class are taken KB at a time
-// with their sums in registers, KB chosen per launch so that one pass covers
-// up to 28 k-pairs and the passes are even (each pass reads I once); the
+// B[kpi][mn][q] = sum_c phase[c][kpi] I[c][row][q], phase = e^{+i k2.L_c}, and for
+// the transposed block B[kpi][nm][q] = sum_c phase_t[c][kpi] I[c][row][q],
+// phase_t = e^{+i (k_cls - k2).L_c} (see the pair transforms), a second table of
+// the same layout after the first; row = mu (mu + 1)/2 + nu, mu >= nu.  One
+// thread per (row, q) element and pass of KB k-pairs (grid y), both sums in
+// registers; a pass covers up to 18 k-pairs and the passes are even (each
+// reads I once; 18 pairs of complex sums are 144 registers, two waves per
+// SIMD), narrower where that leaves few waves (see kphase_width).  The
 // phases are uniform over the wave (scalar loads).  The cells are taken
 // KPH_CB at a time, and the next group's I loads are issued before the
 // current group's multiply-adds (two register sets in turn), so a wave always
@@ -514,9 +516,9 @@ constexpr int KPH_CB = 3;
 template <int KB>
 __device__ __forceinline__ void kphase_sums(const double *__restrict__ I, int64_t ne, int64_t src, bool ok,
                                             const double *__restrict__ phase, int nk, int kpad, int k0,
-                                            double (&sr)[KB], double (&si)[KB]) {
+                                            double (&sr)[KB], double (&si)[KB], double (&tr)[KB], double (&ti)[KB]) {
 #pragma unroll
-  for (int kk = 0; kk < KB; ++kk) sr[kk] = si[kk] = 0.0;
+  for (int kk = 0; kk < KB; ++kk) sr[kk] = si[kk] = tr[kk] = ti[kk] = 0.0;
   if (!ok) return;
   // group g = cells [KPH_CB g, KPH_CB (g + 1)); two register sets in turn
   auto load = [&](int g, double (&xr)[KPH_CB], double (&xi)[KPH_CB]) {
@@ -533,16 +535,20 @@ __device__ __forceinline__ void kphase_sums(const double *__restrict__ I, int64_
       const int c = KPH_CB * g + j;
       const double vr = c < nk ? xr[j] : 0.0, vi = c < nk ? xi[j] : 0.0;
       // the pass's KB phases of cell c are contiguous (zero past nkpi)
-      const double *ph = phase + 2 * ((int64_t)min(c, nk - 1) * kpad + k0);
+      const double *ph = phase + 2 * ((int64_t)min(c, nk - 1) * kpad + k0), *pt = ph + 2 * (int64_t)nk * kpad;
 #pragma unroll
       for (int kk = 0; kk < KB; ++kk) {
-        const double pr = ph[2 * kk], pi = ph[2 * kk + 1];
+        const double pr = ph[2 * kk], pi = ph[2 * kk + 1], ur = pt[2 * kk], ui = pt[2 * kk + 1];
         // two fused multiply-adds per real sum (the written form compiles to
         // a multiply, a fused multiply-add and an add)
         sr[kk] = fma(pr, vr, sr[kk]);
         sr[kk] = fma(-pi, vi, sr[kk]);
         si[kk] = fma(pr, vi, si[kk]);
         si[kk] = fma(pi, vr, si[kk]);
+        tr[kk] = fma(ur, vr, tr[kk]);
+        tr[kk] = fma(-ui, vi, tr[kk]);
+        ti[kk] = fma(ur, vi, ti[kk]);
+        ti[kk] = fma(ui, vr, ti[kk]);
       }
     }
   };
@@ -559,38 +565,65 @@ __device__ __forceinline__ void kphase_sums(const double *__restrict__ I, int64_
   if (g < ng) madd(g, ar, ai);
 }
 
+// (mu, nu) of a row of I: element index in the nao x nao block and in its transpose
+struct RowMN {
+  int64_t mn, nm;
+};
+__device__ __forceinline__ RowMN row_mn(int64_t row, int nao) {
+  int64_t mu = (int64_t)((sqrt(8.0 * (double)row + 1.0) - 1.0) * 0.5);
+  while (mu * (mu + 1) / 2 > row) --mu;
+  while ((mu + 1) * (mu + 2) / 2 <= row) ++mu;
+  const int64_t nu = row - mu * (mu + 1) / 2;
+  return {mu * nao + nu, nu * nao + mu};
+}
+
 template <bool F32, int KB>
 __global__ __launch_bounds__(256) void kphase_kernel(const double *__restrict__ I, const double *__restrict__ phase,
                                                      void *__restrict__ Bout, double *__restrict__ Bhi, int nq_hi,
-                                                     int nk, int nkpi, int nq, int64_t nmn) {
+                                                     int nk, int nkpi, int nq, int nao) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t ne = (int64_t)nq * nmn;
+  const int64_t nmn = (int64_t)nao * nao, ne = (int64_t)nq * ((nmn + nao) / 2);
   if (gid >= ne) return;
   const int q = (int)(gid % nq);
-  const int64_t mn = gid / nq;
-  for (int k0 = 0; k0 < nkpi; k0 += KB) {
-    double sr[KB], si[KB];
-    kphase_sums<KB>(I, ne, gid, true, phase, nk, kphase_kpad(nkpi), k0, sr, si);
+  const RowMN e = row_mn(gid / nq, nao);
+  auto put = [&](int k, int64_t m, double re, double im) {
+    const int64_t o = ((int64_t)k * nmn + m) * nq + q;
+    if constexpr (F32) {
+      float *B = static_cast<float *>(Bout);
+      B[2 * o] = (float)re;
+      B[2 * o + 1] = (float)im;
+      if (Bhi && q < nq_hi) {
+        const int64_t oh = ((int64_t)k * nmn + m) * nq_hi + q;
+        Bhi[2 * oh] = re;
+        Bhi[2 * oh + 1] = im;
+      }
+    } else {
+      double *B = static_cast<double *>(Bout);
+      B[2 * o] = re;
+      B[2 * o + 1] = im;
+    }
+  };
+  {
+    const int k0 = (int)blockIdx.y * KB;
+    double sr[KB], si[KB], tr[KB], ti[KB];
+    kphase_sums<KB>(I, ne, gid, true, phase, nk, kphase_kpad(nkpi), k0, sr, si, tr, ti);
 #pragma unroll
     for (int kk = 0; kk < KB; ++kk)
       if (k0 + kk < nkpi) {
-        const int64_t o = (int64_t)(k0 + kk) * ne + gid;
-        if constexpr (F32) {
-          float *B = static_cast<float *>(Bout);
-          B[2 * o] = (float)sr[kk];
-          B[2 * o + 1] = (float)si[kk];
-          if (Bhi && q < nq_hi) {
-            const int64_t oh = ((int64_t)(k0 + kk) * nmn + mn) * nq_hi + q;
-            Bhi[2 * oh] = sr[kk];
-            Bhi[2 * oh + 1] = si[kk];
-          }
-        } else {
-          double *B = static_cast<double *>(Bout);
-          B[2 * o] = sr[kk];
-          B[2 * o + 1] = si[kk];
-        }
+        put(k0 + kk, e.mn, sr[kk], si[kk]);
+        if (e.nm != e.mn) put(k0 + kk, e.nm, tr[kk], ti[kk]);
       }
   }
+}
+
+// Width of a pass over ne elements: kphase_kb, halved while the launch has fewer
+// than two waves per SIMD.  The chain of a wave is nk KB multiply-adds long: 11 q
+// of a 12-atom cell on a 4x4x4 mesh took 129 us with 16 k-pairs in turn, 23 to 50
+// with these.  A halved width divides the table's stride, so no phase past it is read.
+static int kphase_width(int64_t ne, int nkpi) {
+  int kb = kphase_kb(nkpi);
+  while (kb % 2 == 0 && (ne + 63) / 64 * ((nkpi + kb - 1) / kb) < 2048) kb /= 2;
+  return kb;
 }
 
 // calls launch(std::integral_constant<int, KB>) for KB = kb, 1 <= kb <= KBT:
@@ -601,15 +634,26 @@ void kph_dispatch(int kb, F &&launch) {
   else if constexpr (KBT > 1) kph_dispatch<KBT - 1>(kb, launch);
 }
 
+// nmn = nao^2; I holds the nao (nao + 1)/2 rows mu >= nu
+static int nao_of(int64_t nmn) {
+  int64_t n = (int64_t)std::sqrt((double)nmn);
+  while (n * n > nmn) --n;
+  while ((n + 1) * (n + 1) <= nmn) ++n;
+  return n * n == nmn ? (int)n : -1;
+}
+
 hipError_t launch_kphase(const double *I, const double *phase, void *B, bool f32, double *Bhi, int nq_hi, int nk,
                          int nkpi, int nq, int64_t nmn, hipStream_t stream) {
-  const int64_t ne = (int64_t)nq * nmn;
+  const int nao = nao_of(nmn);
+  if (nao < 0) return hipErrorInvalidValue;
+  const int64_t ne = (int64_t)nq * ((nmn + nao) / 2);
   if (ne == 0 || nkpi == 0) return hipSuccess;
-  const dim3 grid((unsigned)((ne + 255) / 256));
-  kph_dispatch<kKphKbMax>(kphase_kb(nkpi), [&](auto kbc) {
+  const int kb = kphase_width(ne, nkpi);
+  const dim3 grid((unsigned)((ne + 255) / 256), (unsigned)((nkpi + kb - 1) / kb));
+  kph_dispatch<kKphKbMax>(kb, [&](auto kbc) {
     constexpr int KB = decltype(kbc)::value;
-    if (f32) hipLaunchKernelGGL((kphase_kernel<true, KB>), grid, dim3(256), 0, stream, I, phase, B, Bhi, nq_hi, nk, nkpi, nq, nmn);
-    else hipLaunchKernelGGL((kphase_kernel<false, KB>), grid, dim3(256), 0, stream, I, phase, B, Bhi, nq_hi, nk, nkpi, nq, nmn);
+    if (f32) hipLaunchKernelGGL((kphase_kernel<true, KB>), grid, dim3(256), 0, stream, I, phase, B, Bhi, nq_hi, nk, nkpi, nq, nao);
+    else hipLaunchKernelGGL((kphase_kernel<false, KB>), grid, dim3(256), 0, stream, I, phase, B, Bhi, nq_hi, nk, nkpi, nq, nao);
   });
   return hipGetLastError();
 }
@@ -915,41 +959,45 @@ hipError_t launch_asplit(const double *A, int64_t lda, int naux, int nq, int q_e
 
 // kphase_kernel's Bloch sums written in the split format: Xb[kpi][b][mn][4][32],
 // Eb[kpi][b][mn], and the first nq_hi columns in FP64 into Bhi[kpi][mn][nq_hi]
-// (those columns do not enter the exponents).  One thread per (mn, q) of the
+// (those columns do not enter the exponents).  One thread per (row, q) of the
 // padded grid, 32-lane blocks along q, a wavefront per row's exponent group.
 template <int KB>
 __global__ __launch_bounds__(256) void kphase_split_kernel(const double *__restrict__ I,
                                                            const double *__restrict__ phase,
                                                            uint16_t *__restrict__ Xb, int32_t *__restrict__ Eb,
                                                            double *__restrict__ Bhi, int nq_hi, int nk, int nkpi,
-                                                           int nq, int nb, int64_t nmn) {
+                                                           int nq, int nb, int nao) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int l = (int)(gid & 31);
   const int64_t t = gid >> 5;
   const int b = (int)(t % nb);
-  const int64_t mn = t / nb;
+  const int64_t row = t / nb, nmn = (int64_t)nao * nao, nrow = (nmn + nao) / 2;
   const int q = b * kF16Blk + l;
-  const bool row = mn < nmn, ok = row && q < nq;
-  const int64_t ne = (int64_t)nq * nmn, src = mn * nq + q;
+  const bool in = row < nrow, ok = in && q < nq;
+  const RowMN el = row_mn(in ? row : 0, nao);  // one row per wave
+  const int64_t ne = (int64_t)nq * nrow, src = row * nq + q;
   const int kpad = kphase_kpad(nkpi);
-  for (int k0 = 0; k0 < nkpi; k0 += KB) {
-    double sr[KB], si[KB];
-    kphase_sums<KB>(I, ne, src, ok, phase, nk, kpad, k0, sr, si);
+  auto put = [&](int k, int64_t m, double re, double im) {
+    const int e = f16_group_exp(q >= nq_hi ? fmax(fabs(re), fabs(im)) : 0.0);
+    const int64_t rb = ((int64_t)k * nb + b) * nmn + m;
+    if (!in) return;
+    f16_split_store(re, im, e, Xb + rb * 4 * kF16Blk, l);
+    if (l == 0) Eb[rb] = e;
+    if (Bhi && ok && q < nq_hi) {
+      const int64_t oh = ((int64_t)k * nmn + m) * nq_hi + q;
+      Bhi[2 * oh] = re;
+      Bhi[2 * oh + 1] = im;
+    }
+  };
+  {
+    const int k0 = (int)blockIdx.y * KB;
+    double sr[KB], si[KB], tr[KB], ti[KB];
+    kphase_sums<KB>(I, ne, src, ok, phase, nk, kpad, k0, sr, si, tr, ti);
 #pragma unroll
     for (int kk = 0; kk < KB; ++kk)
       if (k0 + kk < nkpi) {  // uniform over the wave
-        const int k = k0 + kk;
-        const int e = f16_group_exp(q >= nq_hi ? fmax(fabs(sr[kk]), fabs(si[kk])) : 0.0);
-        if (row) {
-          const int64_t rb = ((int64_t)k * nb + b) * nmn + mn;
-          f16_split_store(sr[kk], si[kk], e, Xb + rb * 4 * kF16Blk, l);
-          if (l == 0) Eb[rb] = e;
-        }
-        if (Bhi && ok && q < nq_hi) {
-          const int64_t oh = ((int64_t)k * nmn + mn) * nq_hi + q;
-          Bhi[2 * oh] = sr[kk];
-          Bhi[2 * oh + 1] = si[kk];
-        }
+        put(k0 + kk, el.mn, sr[kk], si[kk]);
+        if (el.nm != el.mn) put(k0 + kk, el.nm, tr[kk], ti[kk]);
       }
   }
 }
@@ -957,13 +1005,15 @@ __global__ __launch_bounds__(256) void kphase_split_kernel(const double *__restr
 hipError_t launch_kphase_split(const double *I, const double *phase, uint16_t *Xb, int32_t *Eb, double *Bhi,
                                int nq_hi, int nk, int nkpi, int nq, int64_t nmn, hipStream_t stream) {
   if (nq <= 0 || nmn <= 0 || nkpi <= 0) return hipSuccess;
-  const int nb = f16_nblk(nq);
-  const int64_t n = nmn * nb * kF16Blk;
-  const dim3 grid((unsigned)((n + 255) / 256));
-  kph_dispatch<kKphKbMax>(kphase_kb(nkpi), [&](auto kbc) {
+  const int nb = f16_nblk(nq), nao = nao_of(nmn);
+  if (nao < 0) return hipErrorInvalidValue;
+  const int64_t n = (nmn + nao) / 2 * nb * kF16Blk;
+  const int kb = kphase_width(n, nkpi);
+  const dim3 grid((unsigned)((n + 255) / 256), (unsigned)((nkpi + kb - 1) / kb));
+  kph_dispatch<kKphKbMax>(kb, [&](auto kbc) {
     constexpr int KB = decltype(kbc)::value;
     hipLaunchKernelGGL((kphase_split_kernel<KB>), grid, dim3(256), 0, stream, I, phase, Xb, Eb, Bhi, nq_hi, nk, nkpi, nq,
-                       nb, nmn);
+                       nb, nao);
   });
   return hipGetLastError();
 }
