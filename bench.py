@@ -284,7 +284,7 @@ def main():
     achieved = flops / (t_sr * 1e-3) if t_sr > 0 else 0.0
     roof_sr = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP64_VECTOR / 1e12, "unit": "TFLOP/s",
                "frac": achieved / PEAK_FP64_VECTOR, "traffic": recorded_traffic("sr", problem.name),
-               "kernel": "sr3c_kernel (the 24 angular-momentum classes of one build, on 3 side streams; flops = "
+               "kernel": "sr3c_unit_kernel (the 24 angular-momentum classes of one build, on 3 side streams; flops = "
                          "image-loop terms plus the Hermite contractions)",
                "flops_per_launch": flops, "avg_launch_ms": t_sr}
     # the dominant kernel family by time; the other one is reported beside it

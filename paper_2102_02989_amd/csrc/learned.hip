@@ -2,7 +2,7 @@
 // beside the rigorous bounds of the Supplementary Material, Eqs. S14-S27).
 //
 // Unit of screening: a candidate (aux shell P, AO shell pair, pair image n'),
-// i.e. one iteration of the image loop of sr3c_kernel.  Target: log10 of the
+// i.e. one iteration of the image loop of sr3c_unit_kernel.  Target: log10 of the
 // sum over BvK cells c1 of max |block| that the candidate adds to
 // X[c1][c2][P][mu][nu], an upper bound of its effect on any output element
 // (the Bloch fold combines the c1 blocks with unit-modulus phases).
