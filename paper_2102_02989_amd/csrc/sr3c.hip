@@ -122,6 +122,8 @@ __device__ __forceinline__ void static_for(F &&f) {
 
 constexpr int kUnitCand = 12;   // lattice vectors per lane and pass
 constexpr int kUnitFill = 10;   // and on average when a batch has enough of them
+// (4, 6 and 10 on average: 153, 149 and 143 ms of short range for 8 atoms on a 2x2x2 mesh,
+// 198, 180 and 175 ms for 5 atoms on 2x2x1: a batch's set-up outweighs its even lanes)
 constexpr int kUnitQueue = 128; // pair images waiting in LDS
 constexpr int kUnitFl = 6;      // components per step of the flush
 constexpr int kUnitTrip = 20;   // primitive triples whose constants are held in LDS
