@@ -3,12 +3,12 @@
 // with J^k Hermitian positive definite (a Coulomb metric with q = 0 removed).
 // Per k of the mesh, all k in the same launches, in blocks of 64:
 //   1. Cholesky factor J = L L^H, right-looking: the diagonal block and its
-//      inverse by one workgroup in LDS, the panel below it and the trailing
-//      blocks as 64 x 64 x 64 complex products on the FP64 matrix cores;
+//      inverse by one workgroup in LDS, the panel below it by substitution, the
+//      trailing blocks as 64 x 64 x 64 complex products on the FP64 matrix cores;
 //   2. W = L^{-1} block row by block row, a strip of 16 columns per workgroup.
 // Bound by the chain of n / 64 steps, not by operations: 420 functions on a
 // 2x2x2 mesh took 26.6 ms with one workgroup per k column by column and one
-// thread per column of W, and take 1.3 ms in this form (0.8 ms of it the seven
+// thread per column of W, and take 1.2 ms in this form (0.8 ms of it the seven
 // diagonal blocks, whose 64 dependent columns are the chain).
 // Then for every k-pair Y = W V and d = W^H Y (the forward and backward
 // substitutions of L L^H d = V as products with the substituted inverse, which
@@ -45,9 +45,14 @@ __global__ __launch_bounds__(256) void df_init_kernel(const double2 *__restrict_
 
 // Diagonal block p of every k: Cholesky factor and its inverse in LDS (one
 // workgroup per k).  A pivot below 1e-12 of its diagonal entry of J marks k.
+// The imaginary part of a diagonal entry, zero by definition, holds the sum of
+// |L_jc|^2 of the columns done so far, here and in the trailing update: the entry
+// itself is rounded once, when the sum is taken off it (taken off column by
+// column, the solve's error was 1.3 to 1.7 times as large for well-conditioned
+// metrics of 33 to 160 functions).
 __global__ __launch_bounds__(256) void df_diag_kernel(const double *__restrict__ J, double *__restrict__ L,
                                                       double *__restrict__ W, int n, int p, int *__restrict__ bad) {
-  __shared__ double ar[FB][FBP], ai[FB][FBP], wr[FB][FBP], wi[FB][FBP];
+  __shared__ double ar[FB][FBP], ai[FB][FBP], wr[FB][FBP], wi[FB][FBP], piv;
   const int k = blockIdx.x, tid = threadIdx.x;
   const int p0 = p * FB, nb = min(FB, n - p0);
   double *Lk = L + 2 * (size_t)k * n * n, *Wk = W + 2 * (size_t)k * n * n;
@@ -62,23 +67,36 @@ __global__ __launch_bounds__(256) void df_diag_kernel(const double *__restrict__
   }
   int failed = 0;
   const int tx = tid & 15, ty = tid >> 4;
+  // thread i < nb holds row i's sum of |L_ic|^2 with its rounding error
+  double sum = 0.0, lo = 0.0;
+  __syncthreads();
+  if (tid < nb) sum = ai[tid][tid];
+  if (tid == 0) piv = ar[0][0] - sum;
   for (int j = 0; j < nb; ++j) {
     __syncthreads();
-    const double d = ar[j][j];
+    const double d = piv;
     if (tid == 0 && !(d > 1e-12 * Jk[2 * ((size_t)(p0 + j) * n + p0 + j)])) failed = 1;
     const double s = (d > 0.0) ? sqrt(d) : 1.0, inv = 1.0 / s;
     __syncthreads();
     if (tid > j && tid < nb) {
-      ar[tid][j] *= inv;
-      ai[tid][j] *= inv;
+      const double xr = ar[tid][j] * inv, xi = ai[tid][j] * inv;
+      ar[tid][j] = xr;
+      ai[tid][j] = xi;
+      const double x2 = xr * xr + xi * xi, t = sum + x2, b = t - sum;
+      lo += (sum - (t - b)) + (x2 - b);
+      sum = t;
+      if (tid == j + 1) piv = ar[tid][tid] - (sum + lo);
     }
-    if (tid == j) ar[j][j] = s;
+    if (tid == j) {
+      ar[j][j] = s;
+      ai[j][j] = 0.0;
+    }
     __syncthreads();
     for (int i = j + 1 + ty; i < nb; i += 16)
-      for (int c = j + 1 + tx; c <= i; c += 16) {
+      for (int c = j + 1 + tx; c < i; c += 16) {
         const double xr = ar[i][j], xi = ai[i][j], yr = ar[c][j], yi = ai[c][j];
         ar[i][c] -= xr * yr + xi * yi;  // L_ij conj(L_cj)
-        if (c < i) ai[i][c] -= xi * yr - xr * yi;
+        ai[i][c] -= xi * yr - xr * yi;
       }
   }
   if (tid == 0 && failed) bad[k] = 1;
@@ -115,73 +133,149 @@ __global__ __launch_bounds__(256) void df_diag_kernel(const double *__restrict__
   }
 }
 
-// X Y^H of two 64 x 64 blocks in LDS; wave w holds rows [16 w, 16 w + 16), its
-// four 16-column tiles in cre/cim (result D[lg + 4 v][li])
-__device__ __forceinline__ void df_xyh(const double (&xr)[FB][FBP], const double (&xi)[FB][FBP],
-                                       const double (&yr)[FB][FBP], const double (&yi)[FB][FBP], df_d4 (&cre)[4],
-                                       df_d4 (&cim)[4]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lg = lane >> 4;
-#pragma unroll
-  for (int c = 0; c < 4; ++c)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) cre[c][v] = cim[c][v] = 0.0;
-#pragma unroll 4
-  for (int ks = 0; ks < FB / 4; ++ks) {
-    const int t = 4 * ks + lg;
-    const double a_r = xr[16 * wave + li][t], a_i = xi[16 * wave + li][t];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const double b_r = yr[16 * c + li][t], b_i = yi[16 * c + li][t];
-      // (a_r + i a_i)(b_r - i b_i)
-      cre[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_r, b_r, cre[c], 0, 0, 0);
-      cre[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_i, b_i, cre[c], 0, 0, 0);
-      cim[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_i, b_r, cim[c], 0, 0, 0);
-      cim[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a_r, b_i, cim[c], 0, 0, 0);
+// v of lane src (a constant) of the four
+__device__ __forceinline__ double quad_bcast(double v, int src) {
+  int2 w = *reinterpret_cast<int2 *>(&v);
+  auto at = [src](int x) {
+    switch (src) {
+      case 0: return __builtin_amdgcn_mov_dpp(x, 0x00, 0xf, 0xf, true);
+      case 1: return __builtin_amdgcn_mov_dpp(x, 0x55, 0xf, 0xf, true);
+      case 2: return __builtin_amdgcn_mov_dpp(x, 0xaa, 0xf, 0xf, true);
+      default: return __builtin_amdgcn_mov_dpp(x, 0xff, 0xf, 0xf, true);
     }
-  }
+  };
+  w.x = at(w.x);
+  w.y = at(w.y);
+  return *reinterpret_cast<double *>(&w);
 }
 
-// Blocks below the diagonal block p (PANEL): L_ip = A_ip W_pp^H.  Then the
-// trailing blocks i >= k > p: A_ik -= L_ip L_kp^H.  Grid (nk, row block, column
-// block); every block is read and written by one workgroup.
-template <bool PANEL>
-__global__ __launch_bounds__(256) void df_update_kernel(double *__restrict__ L, const double *__restrict__ W, int n,
-                                                        int p) {
+// Blocks below the diagonal block p: the rows of L_ip L_pp^H = A_ip by forward
+// substitution.  (A product with the explicit inverse W_pp is not as accurate: it
+// alone added a third to the solve's error at 100 to 160 functions.)  Grid (nk,
+// row block); four lanes share a row, lane `part` holding its columns part, part +
+// 4, ...: a chain of 64 scalings, each passed on within the quad.
+__global__ __launch_bounds__(256) void df_panel_kernel(double *__restrict__ L, int n, int p) {
+  __shared__ double lr[FB][FBP], li[FB][FBP], linv[FB];
+  const int tid = threadIdx.x, p0 = p * FB, row = (p + 1 + (int)blockIdx.y) * FB + (tid >> 2), part = tid & 3;
+  double *Lk = L + 2 * (size_t)blockIdx.x * n * n;
+  for (int e = tid; e < FB * FB; e += 256) {  // block p is a whole one: a row block follows it
+    const double2 v = *reinterpret_cast<const double2 *>(Lk + 2 * ((size_t)(p0 + e / FB) * n + p0 + e % FB));
+    lr[e / FB][e % FB] = v.x;
+    li[e / FB][e % FB] = v.y;
+    if (e / FB == e % FB) linv[e / FB] = 1.0 / v.x;
+  }
+  double2 *x = reinterpret_cast<double2 *>(Lk) + (size_t)min(row, n - 1) * n + p0 + part;
+  double xr[FB / 4], xi[FB / 4];
+#pragma unroll
+  for (int c = 0; c < FB / 4; ++c) {
+    const double2 v = x[4 * c];
+    xr[c] = v.x;
+    xi[c] = v.y;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int jb = 0; jb < FB / 4; ++jb)
+#pragma unroll
+    for (int jp = 0; jp < 4; ++jp) {
+      const int j = 4 * jb + jp;
+      const double inv = linv[j], yr = quad_bcast(xr[jb], jp) * inv, yi = quad_bcast(xi[jb], jp) * inv;
+      if (part == jp) {
+        xr[jb] = yr;
+        xi[jb] = yi;
+      }
+#pragma unroll
+      for (int c = 0; c < FB / 4; ++c) {
+        if (c < jb) continue;
+        const bool on = c > jb || part > jp;
+        const double zr = lr[4 * c + part][j], zi = li[4 * c + part][j];
+        const double re = yr * zr + yi * zi, im = yi * zr - yr * zi;  // y conj(L_qj)
+        xr[c] -= on ? re : 0.0;
+        xi[c] -= on ? im : 0.0;
+      }
+    }
+  if (row >= n) return;
+#pragma unroll
+  for (int c = 0; c < FB / 4; ++c) x[4 * c] = make_double2(xr[c], xi[c]);
+}
+
+// Trailing blocks i >= k > p: A_ik -= L_ip L_kp^H.  Grid (nk, row block, column
+// block); every block is read and written by one workgroup.  Wave w holds rows
+// [16 w, 16 w + 16), its four 16-column tiles in cre/cim (result D[lg + 4 v][li]).
+// The products of kUpdCols columns are summed from zero on the matrix cores, then
+// taken off the block: the block's own rounding comes once per 8 columns, and the
+// sums stay small beside it.  (Residual |L L^H - J| against a factorisation column
+// by column, at 130 and 300 functions: 1.6 and 1.2 with all 64 columns in one sum,
+// 1.3 and 1.3 with every product added to the block, 0.95 and 0.8 with 8.)
+constexpr int kUpdCols = 8;
+
+__global__ __launch_bounds__(256) void df_update_kernel(double *__restrict__ L, int n, int p) {
   __shared__ double xr[FB][FBP], xi[FB][FBP], yr[FB][FBP], yi[FB][FBP];
   const int tid = threadIdx.x, p0 = p * FB;
-  const int ib = p + 1 + blockIdx.y, kb = PANEL ? p : p + 1 + (int)blockIdx.z;
+  const int ib = p + 1 + blockIdx.y, kb = p + 1 + (int)blockIdx.z;
   if (kb > ib) return;
   double *Lk = L + 2 * (size_t)blockIdx.x * n * n;
-  const double *Y = PANEL ? W + 2 * (size_t)blockIdx.x * n * n : Lk;
   for (int e = tid; e < FB * FB; e += 256) {
     const int r = e / FB, c = e % FB;
     const int ri = ib * FB + r, rk = kb * FB + r;
     const double2 x = ri < n ? *reinterpret_cast<const double2 *>(Lk + 2 * ((size_t)ri * n + p0 + c))
                              : make_double2(0.0, 0.0);
-    const double2 y = rk < n ? *reinterpret_cast<const double2 *>(Y + 2 * ((size_t)rk * n + p0 + c))
+    const double2 y = rk < n ? *reinterpret_cast<const double2 *>(Lk + 2 * ((size_t)rk * n + p0 + c))
                              : make_double2(0.0, 0.0);
     xr[r][c] = x.x;
     xi[r][c] = x.y;
     yr[r][c] = y.x;
     yi[r][c] = y.y;
   }
-  __syncthreads();
-  df_d4 cre[4], cim[4];
-  df_xyh(xr, xi, yr, yi, cre, cim);
   const int lane = tid & 63, wave = tid >> 6, li = lane & 15, lg = lane >> 4;
+  df_d4 cre[4], cim[4];  // the block, less what has been summed
 #pragma unroll
   for (int c = 0; c < 4; ++c)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int r = ib * FB + 16 * wave + lg + 4 * v, q = kb * FB + 16 * c + li;
-      if (r >= n || q >= n || q > r) continue;
-      double2 *o = reinterpret_cast<double2 *>(Lk + 2 * ((size_t)r * n + q));
-      if (PANEL) {
-        *o = make_double2(cre[c][v], cim[c][v]);
-      } else {
-        const double2 old = *o;
-        *o = make_double2(old.x - cre[c][v], q == r ? 0.0 : old.y - cim[c][v]);
+      const double2 old = (r < n && q <= r) ? *reinterpret_cast<const double2 *>(Lk + 2 * ((size_t)r * n + q))
+                                            : make_double2(0.0, 0.0);
+      cre[c][v] = old.x;
+      cim[c][v] = old.y;
+    }
+  __syncthreads();
+#pragma unroll 2
+  for (int t0 = 0; t0 < FB; t0 += kUpdCols) {
+    df_d4 sre[4], sim[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sre[c][v] = sim[c][v] = 0.0;
+#pragma unroll
+    for (int ks = 0; ks < kUpdCols / 4; ++ks) {
+      const int t = t0 + 4 * ks + lg;
+      const double a_r = xr[16 * wave + li][t], a_i = xi[16 * wave + li][t];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const double b_r = yr[16 * c + li][t], b_i = yi[16 * c + li][t];
+        // (a_r + i a_i)(b_r - i b_i)
+        sre[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_r, b_r, sre[c], 0, 0, 0);
+        sre[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_i, b_i, sre[c], 0, 0, 0);
+        sim[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_i, b_r, sim[c], 0, 0, 0);
+        sim[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a_r, b_i, sim[c], 0, 0, 0);
       }
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const bool diag = ib * FB + 16 * wave + lg + 4 * v == kb * FB + 16 * c + li;
+        cre[c][v] -= diag ? 0.0 : sre[c][v];
+        cim[c][v] -= diag ? -sre[c][v] : sim[c][v];
+      }
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = ib * FB + 16 * wave + lg + 4 * v, q = kb * FB + 16 * c + li;
+      if (r < n && q <= r)
+        *reinterpret_cast<double2 *>(Lk + 2 * ((size_t)r * n + q)) = make_double2(cre[c][v], cim[c][v]);
     }
 }
 
@@ -256,8 +350,8 @@ hipError_t launch_df_factor(const double *J, double *L, double *W, int *bad, int
     hipLaunchKernelGGL(df_diag_kernel, dim3((unsigned)nk), dim3(256), 0, stream, J, L, W, n, p, bad);
     const unsigned rest = (unsigned)(nblk - 1 - p);
     if (rest == 0) break;
-    hipLaunchKernelGGL(df_update_kernel<true>, dim3((unsigned)nk, rest), dim3(256), 0, stream, L, W, n, p);
-    hipLaunchKernelGGL(df_update_kernel<false>, dim3((unsigned)nk, rest, rest), dim3(256), 0, stream, L, W, n, p);
+    hipLaunchKernelGGL(df_panel_kernel, dim3((unsigned)nk, rest), dim3(256), 0, stream, L, n, p);
+    hipLaunchKernelGGL(df_update_kernel, dim3((unsigned)nk, rest, rest), dim3(256), 0, stream, L, n, p);
   }
   if (nblk > 1)
     hipLaunchKernelGGL(df_inverse_kernel, dim3((unsigned)nk, (unsigned)((nblk - 1) * (FB / 16))), dim3(256), 0, stream,
