@@ -2,11 +2,17 @@
 from __future__ import annotations
 
 import concurrent.futures
+import glob
 import hashlib
 import os
 import shutil
 import subprocess
 import sys
+
+try:
+    from . import asm_check
+except ImportError:  # run as a script
+    import asm_check
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -45,12 +51,37 @@ def flags():
             "-Wno-unused-command-line-argument"]
 
 
+def check_assembly(path: str, kernels: bool) -> int:
+    """Refuse device code in which a per-lane instruction precedes an exec restore
+    (asm_check), or whose text the check no longer understands."""
+    with open(path) as fh:
+        restores, found = asm_check.check(fh.read())
+    if found:
+        raise RuntimeError(f"{path}: per-lane instructions in front of an exec restore, where the lanes that left a "
+                           "divergent region lose the value (fewer live registers in the kernel, or another "
+                           "compiler):\n" + "\n".join(f"  {f}, line {n}: {i}" for f, n, i in found))
+    if kernels and restores == 0:
+        raise RuntimeError(f"{path}: no exec restore found; the check of the assembly does not read it")
+    return restores
+
+
 def _compile(src: str, defs=()) -> str:
     obj = os.path.join(BUILD, os.path.basename(src) + ".o")
-    cmd = [hipcc(), *flags(), *defs, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+    tmp = os.path.join(BUILD, "tmp_" + src.replace(".", "_"))
+    shutil.rmtree(tmp, ignore_errors=True)
+    os.makedirs(tmp)
+    # the device code is assembled from the text that -save-temps leaves
+    tobj = os.path.join(tmp, os.path.basename(obj))
+    cmd = [hipcc(), *flags(), *defs, "-save-temps=obj", "-x", "hip", "-c", os.path.join(CSRC, src), "-o", tobj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    asm = glob.glob(os.path.join(tmp, f"*-hip-amdgcn-amd-amdhsa-{ARCH}*.s"))
+    if len(asm) != 1:
+        raise RuntimeError(f"{src}: expected one device assembly text under {tmp}, found {len(asm)}")
+    check_assembly(asm[0], src.endswith(".hip"))
+    os.replace(tobj, obj)
+    shutil.rmtree(tmp)
     return obj
 
 
