@@ -34,6 +34,7 @@
 #include "boys.h"
 #include "device_math.h"
 #include "kernels.h"
+#include "lanes.h"
 #include "plan.h"
 
 namespace rsgdf {
@@ -405,15 +406,16 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
       const int cj = in ? (cwj & kUnitClsMask) : -1;
       const int cn = lane + 1 < qn ? (s_qcw[(qh + lane + 1) & (kUnitQueue - 1)] & kUnitClsMask)
                                    : (nxt >= nimg_all ? -2 : cj);
-      // lattice vectors per cell of the images up to this one (sphere volume)
-      const float rj = (float)((cwj >> kUnitClsBits) + 1);
-      float cum = in ? rj * rj * rj * (float)(4.18879020478639098 * prm.dR * prm.dR * prm.dR / (lat.vol * nk)) : 0.f;
+      // weight of the images up to this one; times vec, their lattice vectors per
+      // cell (sphere volume)
+      int cum = in ? sr_image_weight(cwj >> kUnitClsBits) : 0;
+      const float vec = (float)(4.18879020478639098 * prm.dR * prm.dR * prm.dR / (lat.vol * nk));
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
-        const float up = __shfl_up(cum, o, 64);
-        cum += lane >= o ? up : 0.f;
+        const int up = __shfl_up(cum, o, 64);
+        cum += lane >= o ? up : 0;
       }
-      const unsigned long long full = __ballot(in && cum >= (float)(rows * kUnitFill));
+      const unsigned long long full = __ballot(in && (float)cum * vec >= (float)(rows * kUnitFill));
       // (the class after the queue's last image is known only once the list has ended)
       const int nibmax = logging ? 1 : min(min(rows, nxt >= nimg_all ? 64 : 63), full ? __ffsll((long long)full) : 64);
       const unsigned long long lim = nibmax >= 64 ? ~0ull : ((1ull << nibmax) - 1ull);
@@ -426,8 +428,8 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
       if (lastj) s_runcls[__popcll(ends & ((1ull << lane) - 1ull))] = cj;
       // rows per image in proportion to its lattice vectors, at least one each:
       // image j owns rows [s_rowend[j-1], s_rowend[j])
-      const float tot = __shfl(cum, m - 1, 64);
-      if (lane < m) s_rowend[lane] = lane == m - 1 ? rows : lane + 1 + (int)((float)(rows - m) * (cum / tot));
+      const float inv_tot = 1.0f / (float)__shfl(cum, m - 1, 64);
+      if (lane < m) s_rowend[lane] = sr_row_end(lane, m, rows, cum, inv_tot);
     }
     wave_sync();
     int slot = 0;

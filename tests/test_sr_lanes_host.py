@@ -1,0 +1,75 @@
+"""Host tests of the rules by which the short-range kernel deals out its lanes
+(csrc/lanes.h), compiled for the CPU."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2102_02989_amd", "csrc")
+SRC = """
+#include "lanes.h"
+extern "C" void row_ends(const int *wm, int m, int rows, int *out) {
+  int tot = 0, cum = 0;
+  for (int j = 0; j < m; ++j) tot += rsgdf::sr_image_weight(wm[j]);
+  const float inv = 1.0f / (float)tot;
+  for (int j = 0; j < m; ++j) {
+    cum += rsgdf::sr_image_weight(wm[j]);
+    out[j] = rsgdf::sr_row_end(j, m, rows, cum, inv);
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lanes(tmp_path_factory):
+    if not shutil.which("g++") or not os.path.isdir("/opt/rocm/include/hip"):
+        pytest.skip("g++ and the HIP headers are needed")
+    d = tmp_path_factory.mktemp("lanes")
+    (d / "l.cpp").write_text(SRC)
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", CSRC,
+           "-D__align__(n)=__attribute__((aligned(n)))", "-o", str(d / "l.so"), str(d / "l.cpp")]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    return ctypes.CDLL(str(d / "l.so"))
+
+
+def _row_ends(lanes, wm, rows):
+    wm = np.ascontiguousarray(wm, np.int32)
+    out = np.zeros(len(wm), np.int32)
+    p = ctypes.POINTER(ctypes.c_int)
+    lanes.row_ends(wm.ctypes.data_as(p), len(wm), rows, out.ctypes.data_as(p))
+    return out
+
+
+def test_every_image_gets_a_row(lanes):
+    """Near images with hundreds of windows beside far ones with a few: the running
+    sum of volumes in single precision is not monotone there (64 values, summed in the
+    order of a wave's scan), and images were left without a row."""
+    rng = np.random.default_rng(0)
+    decreasing = 0
+    for _ in range(4000):
+        rows = int(rng.integers(2, 65))
+        m = int(rng.integers(1, rows + 1))
+        far = rng.random(m) < rng.choice([0.1, 0.5, 0.9])
+        wm = np.where(far, rng.integers(0, 6, m), rng.integers(75, 256, m))
+        e = _row_ends(lanes, wm, rows)
+        assert e[-1] == rows and e[0] >= 1 and np.all(np.diff(e) >= 1), (rows, wm.tolist(), e.tolist())
+        f = (np.float32(wm + 1) ** 3 * np.float32(10.0 ** rng.uniform(-8, 0))).astype(np.float32)
+        o = 1
+        while o < m:
+            f[o:] = f[o:] + f[:-o].copy()
+            o *= 2
+        decreasing += bool(np.any(np.diff(f) < 0))
+    assert decreasing > 100  # the inputs are of the kind that matters
+    for rows in (1, 7, 64):  # the extremes
+        for wm in ([255] * rows, [0] * rows, [255] + [0] * (rows - 1), [0] * (rows - 1) + [255]):
+            e = _row_ends(lanes, wm, rows)
+            assert e.tolist() == list(range(1, rows + 1))
+
+
+def test_rows_follow_the_weights(lanes):
+    """One image of weight 27 against one of 1 over 64 rows: 62 rows are shared 27 to 1."""
+    assert _row_ends(lanes, [2, 0], 64).tolist() == [1 + 62 * 27 // 28, 64]
