@@ -485,10 +485,8 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
       // ---- the lane's next lattice vectors inside the screening windows
       int cnt = 0;
       while (q < nbox && cnt < kUnitCand) {
-        const int j0 = (int)(((float)q + 0.5f) * inv12);
-        const int r0 = q - j0 * dim1 * dim2;
-        const int j1 = (int)(((float)r0 + 0.5f) * inv2);
-        const int j2 = r0 - j1 * dim2;
+        int j0, j1, j2;
+        sr_box_entry(q, dim1, dim2, inv12, inv2, j0, j1, j2);
         const int M0 = i1x + lat.n[0] * (lo0 + j0), M1 = i1y + lat.n[1] * (lo1 + j1),
                   M2 = i1z + lat.n[2] * (lo2 + j2);
         const double mx = X0x + M0 * a[0] + M1 * a[3] + M2 * a[6];

@@ -20,6 +20,20 @@ extern "C" void row_ends(const int *wm, int m, int rows, int *out) {
     out[j] = rsgdf::sr_row_end(j, m, rows, cum, inv);
   }
 }
+extern "C" long box_errors(int dim0, int dim1, int dim2, int near) {
+  const int d12 = dim1 * dim2, nbox = dim0 * d12;
+  const float inv12 = 1.0f / (float)d12, inv2 = 1.0f / (float)dim2;
+  long bad = 0;
+  for (int j0 = 0; j0 < dim0; ++j0)
+    for (int k = -near; k <= near; ++k) {
+      const int q = j0 * d12 + k;
+      if (q < 0 || q >= nbox) continue;
+      int a, b, c;
+      rsgdf::sr_box_entry(q, dim1, dim2, inv12, inv2, a, b, c);
+      bad += a != q / d12 || b != q / dim2 % dim1 || c != q % dim2;
+    }
+  return bad;
+}
 """
 
 
@@ -73,3 +87,12 @@ def test_every_image_gets_a_row(lanes):
 def test_rows_follow_the_weights(lanes):
     """One image of weight 27 against one of 1 over 64 rows: 62 rows are shared 27 to 1."""
     assert _row_ends(lanes, [2, 0], 64).tolist() == [1 + 62 * 27 // 28, 64]
+
+
+@pytest.mark.parametrize("dims", [(1, 1, 1), (3, 5, 7), (1, 1, 1000), (1000, 1, 1), (161, 161, 161), (172, 173, 171),
+                                  (257, 256, 255), (400, 401, 399), (1000, 999, 1001), (1001, 1000, 1000)])
+def test_box_entries(lanes, dims):
+    """Boxes of lattice vectors up to the size the planner accepts (|M| < 500): every
+    entry near a plane's end has the indices of the whole-number division."""
+    lanes.box_errors.restype = ctypes.c_long
+    assert lanes.box_errors(*dims, min(4 * dims[2] + 200, dims[1] * dims[2])) == 0
