@@ -133,7 +133,7 @@ typedef struct rsgdf_stats {
   double sr_flops;       /* algorithmic FP64 operations of the SR kernels (static counts):  the
                             image loop's per-term count times the evaluated terms, plus the
                             Hermite contraction's count per (pair image, primitive triple, BvK
-                            cell group) times the contractions performed                    */
+                            cell) with a lattice vector                                     */
   double t_lr_gemm_ms;   /* G-space contraction kernels alone                               */
   int64_t n_screen_candidates; /* (aux shell, AO pair, pair image) candidates (learned mode) */
   int64_t n_screen_skipped;    /* candidates the network dropped                            */

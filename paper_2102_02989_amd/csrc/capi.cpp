@@ -1387,7 +1387,7 @@ int Job::prepare(hipStream_t st, double mem_frac) {
       const int nblk = ncart_h(sP.l) * ncart_h(sA.l) * ncart_h(sB.l);
       const double ev = 2.0 * nherm(Lt) + 2.0 * ncart_h(sP.l) * nherm(lab) * nkx + 2.0 * nblk * nherm(lab);
       const double nranges = std::ceil((double)nk / std::min(nk, sr_cells_per_wave(sP.l, sA.l, sB.l)));
-      est[t] = (double)sA.nprim * sB.nprim * sP.nprim * (double)nimg * (nm * sr_term_flops(Lt) + 13.6 * nranges * ev);
+      est[t] = (double)sA.nprim * sB.nprim * sP.nprim * (double)nimg * (nm * sr_term_work(Lt) + 13.6 * nranges * ev);
     }, 1024);
     double tot = 0.0;
     for (int64_t t = 0; t < ntrip; ++t) tot += est[t];
@@ -3120,7 +3120,7 @@ int rsgdf_plan_features_acut(const rsgdf_cell *cell, const rsgdf_basis *basis, c
       const double nranges = std::ceil((double)nk / std::min(nk, sr_cells_per_wave(sP.l, sA.l, sB.l)));
       const double npp = (double)sA.nprim * sB.nprim - (double)ndiff(sA, hp.ao_exp) * ndiff(sB, hp.ao_exp);
       const double np3 = npp * (sP.nprim - ndiff(sP, hp.ax_exp)) * (double)nimg;
-      sr += np3 * (nm * sr_term_flops(Lt) + 13.6 * nranges * ev);
+      sr += np3 * (nm * sr_term_work(Lt) + 13.6 * nranges * ev);
       sr_terms += np3 * nm;
     }
   // long range: q vectors, pair-transform candidates, contraction flops, per

@@ -74,30 +74,39 @@ __host__ __device__ constexpr int hermite_R_flops(int L) {
   return f;
 }
 
-// Static per-term FP64 operation count of the image loop for class L:
-// position and T (13) + attenuated Boys values (two degree-12 polynomials,
-// two downward recursions, theta scaling) + (-2 rho)^n scaling (2L) +
-// Hermite recursion + image accumulation (nherm(L)).  An exp counts as one.
+// Static per-term FP64 operation count of the image loop for class L: position and
+// T (13), the two Boys values of boys_fine (interval 3, degree-7 series 16, for L >
+// 0 the series of e^{-u} with its centre value 17 and the downward recursion 3 L),
+// theta scaling 3 (L + 1), (-2 rho)^n scaling 2 L, Hermite recursion and image
+// accumulation (nherm(L)).
 inline int sr_term_flops(int L) {
   const int geo = 13;
-  const int boys = 2 * (2 * kBoysPolyDeg + 3 * L + 1) + 3 * (L + 1);
+  const int boys = 2 * (3 + 16 + (L > 0 ? 17 : 0) + 3 * L) + 3 * (L + 1);
   return geo + boys + 2 * L + hermite_R_flops(L) + nherm(L);
 }
 
 // Static FP64 operation count of the McMurchie-Davidson contraction of one
-// (pair image, primitive triple, BvK cell group): the aux pass
-// W[ic][tuv] = sum over the even aux Hermite orders of E^c_x E^c_y E^c_z R
-// (NW = ncart(lP) nherm(la + lb) entries, (KX + 1)^3 products each, KX =
-// lP / 2), then the pair pass, each Cartesian component (ncart of all three)
-// summing E^ab_x E^ab_y E^ab_z W over the nherm(la + lb) Hermite orders,
-// times the triple's prefactor.
+// (pair image, primitive triple, BvK cell): for every aux Hermite order (sr_ntau)
+// and AO component the sums over E^ab_x E^ab_y E^ab_z R, one axis in the other, and
+// the factor of the order.
 inline int sr_contr_flops(int lP, int la, int lb) {
-  const int lab = la + lb, kx = lP / 2 + 1;
-  const int nw = ncart(lP) * nherm(lab);
-  const int w = nw * (2 * kx * kx * kx + 3 * kx * kx);
-  const int nblk = ncart(lP) * ncart(la) * ncart(lb);
-  const int c = nblk * (2 * nherm(lab) + (lab + 1) * (lab + 2) + 2 * (lab + 1) + 1);
-  return w + c;
+  int ab = 0;
+  for (int ax = la; ax >= 0; --ax)
+    for (int ay = la - ax; ay >= 0; --ay)
+      for (int bx = lb; bx >= 0; --bx)
+        for (int by = lb - bx; by >= 0; --by) {
+          const int nx = ax + bx + 1, ny = ay + by + 1, nz = la - ax - ay + lb - bx - by + 1;
+          ab += 2 * (nx * ny * nz + nx * ny + nx + 1);
+        }
+  return sr_ntau(lP) * ab;
+}
+
+// The planner's unit of work for a term: the operations with a degree-12 series per
+// Boys value.
+inline int sr_term_work(int L) {
+  const int geo = 13;
+  const int boys = 2 * (2 * kBoysPolyDeg + 3 * L + 1) + 3 * (L + 1);
+  return geo + boys + 2 * L + hermite_R_flops(L) + nherm(L);
 }
 
 // Packed shell (AO or aux).  a_d, c_d: exponent and 1s-equivalent amplitude
