@@ -1045,7 +1045,7 @@ struct Job {
   int nk = 0, nkp = 0, npair = 0, nxs = 0, nb = 0;
   int64_t nao = 0, naux = 0, nao2 = 0, need = 0;
   double t_plan = 0.0;
-  DBuf d_ao, d_ax, d_aoe, d_aoc, d_aoc1, d_axe, d_axc, d_axc1, d_pairs, d_coff, d_nsr, d_img, d_boys, d_boysf, d_plist;
+  DBuf d_ao, d_ax, d_aoe, d_aoc, d_aoc1, d_axe, d_axc, d_axc1, d_pairs, d_coff, d_nsr, d_img, d_boysf, d_plist;
   int32_t plist_grp[7] = {};  // d_plist offsets of the (l(sa), l(sb)) groups dd, dp, ds, pp, ps, ss
   DBuf d_outbuf;
   double *d_out = nullptr;
@@ -1201,8 +1201,6 @@ int Job::prepare(hipStream_t st, double mem_frac) {
   HIPCHK(upload(d_coff, hp.cls_off, st));
   HIPCHK(upload(d_nsr, hp.nsr, st));
   HIPCHK(upload(d_img, hp.img, st));
-  const std::vector<double> boys = boys_poly_table();
-  HIPCHK(upload(d_boys, boys, st));
   HIPCHK(upload(d_boysf, boys_fine_table(), st));
 
   if (logging || tune) {
@@ -1523,7 +1521,6 @@ int Job::prepare(hipStream_t st, double mem_frac) {
   base.dR = hp.scr.dR;
   base.ncell_nf = hp.scr.ncell_nf;
   base.ncell_r0 = hp.scr.r0;
-  base.boys = d_boys.as<double>();
   base.boys_fine = d_boysf.as<double>();
   base.acut = acut;
   base.X = d_X.as<double>();

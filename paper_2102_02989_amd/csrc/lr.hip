@@ -155,8 +155,8 @@ __device__ __forceinline__ void pairft_binned_one(const PairFTParams &pp, int ip
   bool live[QP];
   double qx[QP], qy[QP], qz[QP], q2[QP];
   // The skip tests use the wave's extreme values (largest amax and |q|,
-  // smallest q^2), so they bound every term of every lane and every lane takes
-  // the same branch.
+  // smallest q^2), so they bound every term of every lane, and the lanes of the plain
+  // form take the same branch (those of the sliced form walk different images).
   double am = 0.0, q2w = 1e300, qnw = 0.0;
 #pragma unroll
   for (int s = 0; s < QP; ++s) {

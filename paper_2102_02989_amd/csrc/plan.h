@@ -184,7 +184,6 @@ struct SRParams {
   Lattice lat;
   double omega, eps, dR;
   double ncell_nf, ncell_r0;  // N_cell model of Eq. S19
-  const double *boys;       // [L = 0..kMaxL][kBoysIntervals][kBoysPolyDeg + 1]
   const double *boys_fine;  // [L = 0..kMaxL][kBoysFineTab]
   double acut;              // > 0: compact/diffuse split (primitive triples with a diffuse aux
                             // primitive or two diffuse AO primitives are left to Eq. M15)
