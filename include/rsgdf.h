@@ -132,8 +132,9 @@ typedef struct rsgdf_stats {
   int64_t bytes_out;     /* output bytes written                                            */
   double sr_flops;       /* algorithmic FP64 operations of the SR kernels (static counts):  the
                             image loop's per-term count times the evaluated terms, plus the
-                            Hermite contraction's count per (pair image, primitive triple, BvK
-                            cell) with a lattice vector                                     */
+                            Hermite contraction's count times the contractions performed (one
+                            per primitive triple and lane with lattice vectors of its (pair
+                            image, BvK cell): at most 12 terms each)                        */
   double t_lr_gemm_ms;   /* G-space contraction kernels alone                               */
   int64_t n_screen_candidates; /* (aux shell, AO pair, pair image) candidates (learned mode) */
   int64_t n_screen_skipped;    /* candidates the network dropped                            */

@@ -85,10 +85,10 @@ inline int sr_term_flops(int L) {
   return geo + boys + 2 * L + hermite_R_flops(L) + nherm(L);
 }
 
-// Static FP64 operation count of the McMurchie-Davidson contraction of one
-// (pair image, primitive triple, BvK cell): for every aux Hermite order (sr_ntau)
-// and AO component the sums over E^ab_x E^ab_y E^ab_z R, one axis in the other, and
-// the factor of the order.
+// Static FP64 operation count of one McMurchie-Davidson contraction (a lane's share
+// of a pair image and BvK cell, for a primitive triple): for every aux Hermite order
+// (sr_ntau) and AO component the sums over E^ab_x E^ab_y E^ab_z R, one axis in the
+// other, and the factor of the order.
 inline int sr_contr_flops(int lP, int la, int lb) {
   int ab = 0;
   for (int ax = la; ax >= 0; --ax)

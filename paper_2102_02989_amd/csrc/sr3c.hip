@@ -128,7 +128,6 @@ constexpr int kUnitFill = 10;   // and on average when a batch has enough of the
 constexpr int kUnitQueue = 128; // pair images waiting in LDS
 constexpr int kUnitFl = 6;      // components per step of the flush
 constexpr int kUnitTrip = 20;   // primitive triples whose constants are held in LDS
-constexpr unsigned kUnitPassed = 1u << 31;  // marks the passes after a batch's first
 constexpr int kUnitWaves = 4;   // waves per workgroup (they share the Boys table and nothing else)
 
 // item constants in LDS: centres A, B, C; window test; diffuse pair centre
@@ -224,7 +223,7 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
     float nf[kSRWinCap];
     int qii[kUnitQueue], qcw[kUnitQueue];  // pair image index; class | (largest window << kUnitClsBits)
     int rowcls[64], runcls[64], c2[64], rowend[64];
-    unsigned cnt[4 * 64];  // per lane: terms, contractions, lattice vectors; triples of the batch's first pass
+    unsigned cnt[3 * 64];  // per lane: terms, contractions, lattice vectors
     double u[uNum];        // the item's constants, read where they are used: in
     int n[nNum];           // registers they would push the lanes' sums to scratch
     double R[WIDE ? kWideUnits * RS : 1];         // wide classes: Hermite sums [unit][h]
@@ -482,7 +481,6 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
 
     const double inv_dR = 1.0 / prm.dR;
     int q = share;
-    s_cnt[3 * 64 + lane] = 0;
     for (;;) {
       // ---- the lane's next lattice vectors inside the screening windows
       int cnt = 0;
@@ -555,7 +553,7 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
         }
         wave_sync();  // (the constants below are read again, not kept over the loop)
         s_cnt[lane] += (unsigned)nt;
-        s_cnt[3 * 64 + lane] += (unsigned)(nt > 0);
+        s_cnt[64 + lane] += (unsigned)(nt > 0);
         if constexpr (WIDE) {
           // A few rows at a time: their lanes put the Hermite sums and E^ab (with
           // the prefactor in the x rows) into LDS, then lane (cell, tau) gathers
@@ -659,18 +657,6 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
         });
         }
       }
-      // contractions, counted once per unit: by its first lane with a vector (before:
-      // the lanes of the same cell in the rows row0 to row - 1), in the first pass (a
-      // lane with any has one there; what later passes add lies above the mark)
-      if (tt1 > 0) {
-        unsigned long long col = 1;
-        for (int o = ncb; o < 64; o <<= 1) col |= col << o;
-        const unsigned long long before =
-            (col << gl) & ((1ull << lane) - 1ull) & ~((1ull << (row0 * ncb)) - 1ull);
-        const unsigned n = s_cnt[3 * 64 + lane];
-        s_cnt[64 + lane] += (__ballot(cnt > 0) & before) || n >= kUnitPassed ? 0u : n;
-      }
-      s_cnt[3 * 64 + lane] = kUnitPassed;
       if (!__any(q < nbox)) break;
     }
 
