@@ -1378,16 +1378,7 @@ int Job::prepare(hipStream_t st, double mem_frac) {
       const Shell &sA = hp.ao[pp.sa], &sB = hp.ao[pp.sb], &sP = hp.ax[tr.aux];
       const int64_t nimg = nimg_pair[tr.pair];
       const double nm = 4.18879020478639098 * tr.rc_cut * tr.rc_cut * tr.rc_cut / L.vol + 1.0;
-      const int Lt = sP.l + sA.l + sB.l;
-      // per (primitive triple, pair image, cell range): the group reduction, the
-      // W table and the Cartesian components of the contraction, in flops; the
-      // weight 13.6 is the least-squares ratio of the two costs over the 24
-      // classes' standalone durations on the 8-atom 2x2x2 workload
-      const int lab = sA.l + sB.l, nkx = (sP.l / 2 + 1) * (sP.l / 2 + 1) * (sP.l / 2 + 1);
-      const int nblk = ncart_h(sP.l) * ncart_h(sA.l) * ncart_h(sB.l);
-      const double ev = 2.0 * nherm(Lt) + 2.0 * ncart_h(sP.l) * nherm(lab) * nkx + 2.0 * nblk * nherm(lab);
-      const double nranges = std::ceil((double)nk / std::min(nk, sr_cells_per_wave(sP.l, sA.l, sB.l)));
-      est[t] = (double)sA.nprim * sB.nprim * sP.nprim * (double)nimg * (nm * sr_term_work(Lt) + 13.6 * nranges * ev);
+      est[t] = (double)sA.nprim * sB.nprim * sP.nprim * (double)nimg * sr_item_work(sP.l, sA.l, sB.l, nm, nk);
     }, 1024);
     double tot = 0.0;
     for (int64_t t = 0; t < ntrip; ++t) tot += est[t];
@@ -3112,14 +3103,9 @@ int rsgdf_plan_features_acut(const rsgdf_cell *cell, const rsgdf_basis *basis, c
       for (int c = 0; c < nk; ++c) nimg += hp.nsr[(size_t)ip * nk + c];
       const double rc_cut = hp.rc_t[t];
       const double nm = 4.18879020478639098 * rc_cut * rc_cut * rc_cut / L.vol + 1.0;
-      const int Lt = sP.l + sA.l + sB.l;
-      const int lab = sA.l + sB.l, nkx = (sP.l / 2 + 1) * (sP.l / 2 + 1) * (sP.l / 2 + 1);
-      const int nblk = ncart_h(sP.l) * ncart_h(sA.l) * ncart_h(sB.l);
-      const double ev = 2.0 * nherm(Lt) + 2.0 * ncart_h(sP.l) * nherm(lab) * nkx + 2.0 * nblk * nherm(lab);
-      const double nranges = std::ceil((double)nk / std::min(nk, sr_cells_per_wave(sP.l, sA.l, sB.l)));
       const double npp = (double)sA.nprim * sB.nprim - (double)ndiff(sA, hp.ao_exp) * ndiff(sB, hp.ao_exp);
       const double np3 = npp * (sP.nprim - ndiff(sP, hp.ax_exp)) * (double)nimg;
-      sr += np3 * (nm * sr_term_work(Lt) + 13.6 * nranges * ev);
+      sr += np3 * sr_item_work(sP.l, sA.l, sB.l, nm, nk);
       sr_terms += np3 * nm;
     }
   // long range: q vectors, pair-transform candidates, contraction flops, per

@@ -101,12 +101,14 @@ inline int sr_contr_flops(int lP, int la, int lb) {
   return sr_ntau(lP) * ab;
 }
 
-// The planner's unit of work for a term: the operations with a degree-12 series per
-// Boys value.
-inline int sr_term_work(int L) {
-  const int geo = 13;
-  const int boys = 2 * (2 * kBoysPolyDeg + 3 * L + 1) + 3 * (L + 1);
-  return geo + boys + 2 * L + hermite_R_flops(L) + nherm(L);
+// The planner's work estimate per pair image and primitive triple: nm terms and a
+// contraction for every BvK cell with a lattice vector, by their operations.  Fitted to
+// the classes' durations one at a time, a contraction's operation weighs 1.1 times a
+// term's (8 atoms 2x2x2, 24 classes) or 0.7 times (4 atoms 3x3x3).  The split of the work
+// that follows from 1 is the fastest: with 0.5, 2 and 4 times the weight 3 atoms 1x3x2
+// took 2, 4 and 3% longer, 5 atoms 2x2x1 1, 4 and 3%, the batch of 8 cells the same.
+inline double sr_item_work(int lP, int la, int lb, double nm, int nk) {
+  return nm * sr_term_flops(lP + la + lb) + (nm < nk ? nm : (double)nk) * sr_contr_flops(lP, la, lb);
 }
 
 // Packed shell (AO or aux).  a_d, c_d: exponent and 1s-equivalent amplitude
