@@ -1,7 +1,9 @@
-// lanes.h -- integer rules by which the short-range kernel deals out its lanes,
-// for the device and for host tests.
+// lanes.h -- integer rules by which the short-range kernel and the pair transforms
+// deal out their lanes, for the device and for host tests.
 #pragma once
 #include <hip/hip_runtime.h>
+
+#include <cstdint>
 
 namespace rsgdf {
 
@@ -32,6 +34,42 @@ __host__ __device__ inline void sr_box_entry(int q, int dim1, int dim2, float in
   r0 -= fix * d12;
   j1 = (int)(((float)r0 + 0.5f) * inv2);
   j2 = r0 - j1 * dim2;
+}
+
+// q values per lane of the pair transforms: the image-dependent work of a term (Gaussian factor,
+// bound, pair centre, E coefficients) is the same for every q, so the lanes of
+// the lighter classes take several q each and do it once for all of them (s-s
+// eight, p-s four, up to l_a + l_b = 3 two; the d-d accumulators leave no
+// registers for more).  Measured on the 8-atom 3x3x3 workload: s-s 4 -> 8 and
+// p-s 2 -> 4 took the long-range phase from 5.39 to 5.10 s; p-s 6 or
+// l_a + l_b = 2 at four were slower.
+__host__ __device__ constexpr int pairft_qpl(int la, int lb) {
+  return la + lb == 0 ? 8 : (la + lb == 1 ? 4 : (la + lb <= 3 ? 2 : 1));
+}
+
+constexpr int kPairFtWaves = 4;  // waves of a workgroup that share a pair's terms (sliced form)
+
+// How a class's q are dealt out.  With at least 64 q the lanes are q, and each
+// takes as many of them as leave 8 waves per SIMD (a term's q-independent work
+// is done once per lane: at 2400 q per class and 45 to 78 pairs, 8 q per lane
+// left 2300 waves, the longest of which the launch waited for: 1x3x2 mesh, 52 ms
+// of pair transforms, 26 with this rule).  With fewer than 64 q (a Gamma or small-omega build has 6
+// to 30) the lanes beyond them would idle: they share the terms instead, and so
+// do four waves of a workgroup where the launch has few of them.
+struct PairFtShape {
+  int qp, nql, waves;  // q per lane; nql > 0: sliced form
+};
+inline PairFtShape pairft_shape(int64_t nx, int nq, int qpmax) {
+  const int64_t nw = nx * ((nq + 63) / 64);
+  if (nq < 64) {
+    int nql = 1;
+    while (nql < nq) nql *= 2;
+    return {1, nql, nw < 2048 ? kPairFtWaves : 1};
+  }
+  if (nw < 2048) return {1, 64, kPairFtWaves};
+  int qp = qpmax;
+  while (qp > 1 && nx * ((nq + 64 * qp - 1) / (64 * qp)) < 8192) qp /= 2;
+  return {qp, 0, 1};
 }
 
 }  // namespace rsgdf

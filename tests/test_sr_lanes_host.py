@@ -1,14 +1,12 @@
 """Host tests of the rules by which the short-range kernel deals out its lanes
 (csrc/lanes.h), compiled for the CPU."""
 import ctypes
-import os
-import shutil
-import subprocess
 
 import numpy as np
 import pytest
 
-CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2102_02989_amd", "csrc")
+import lanes_util
+
 SRC = """
 #include "lanes.h"
 extern "C" void row_ends(const int *wm, int m, int rows, int *out) {
@@ -39,15 +37,7 @@ extern "C" long box_errors(int dim0, int dim1, int dim2, int near) {
 
 @pytest.fixture(scope="module")
 def lanes(tmp_path_factory):
-    if not shutil.which("g++") or not os.path.isdir("/opt/rocm/include/hip"):
-        pytest.skip("g++ and the HIP headers are needed")
-    d = tmp_path_factory.mktemp("lanes")
-    (d / "l.cpp").write_text(SRC)
-    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", CSRC,
-           "-D__align__(n)=__attribute__((aligned(n)))", "-o", str(d / "l.so"), str(d / "l.cpp")]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr[-3000:]
-    return ctypes.CDLL(str(d / "l.so"))
+    return lanes_util.build(tmp_path_factory.mktemp("lanes"), SRC)
 
 
 def _row_ends(lanes, wm, rows):
