@@ -134,7 +134,8 @@ typedef struct rsgdf_stats {
                             image loop's per-term count times the evaluated terms, plus the
                             Hermite contraction's count times the contractions performed (one
                             per primitive triple and lane with lattice vectors of its (pair
-                            image, BvK cell): at most 12 terms each)                        */
+                            image, BvK cell); one for all lanes of the pair image and cell in
+                            the classes (d|dd), (f|dp), (f|dd))                             */
   double t_lr_gemm_ms;   /* G-space contraction kernels alone                               */
   int64_t n_screen_candidates; /* (aux shell, AO pair, pair image) candidates (learned mode) */
   int64_t n_screen_skipped;    /* candidates the network dropped                            */

@@ -121,10 +121,6 @@ __device__ __forceinline__ void static_for(F &&f) {
   }
 }
 
-constexpr int kUnitCand = 12;   // lattice vectors per lane and pass
-constexpr int kUnitFill = 10;   // and on average when a batch has enough of them
-// (4, 6 and 10 on average: 153, 149 and 143 ms of short range for 8 atoms on a 2x2x2 mesh,
-// 198, 180 and 175 ms for 5 atoms on 2x2x1: a batch's set-up outweighs its even lanes)
 constexpr int kUnitQueue = 128; // pair images waiting in LDS
 constexpr int kUnitFl = 6;      // components per step of the flush
 constexpr int kUnitTrip = 20;   // primitive triples whose constants are held in LDS
@@ -173,6 +169,22 @@ __host__ __device__ constexpr int sr_unit_waves(int LP, int LA, int LB) {
   return d <= 30 ? 3 : (d <= 75 ? 2 : 1);
 }
 
+// Lattice vectors that a lane lists, and contracts at once: as many as leave the
+// workgroups that the registers allow their LDS (one of 108 to 159 KB per CU where a
+// lane has the registers of a SIMD to itself, else two of 76 KB).  With 12 in every class
+// the contractions, one per pass, were the work where a unit has hundreds of vectors:
+// 8 atoms 2x2x2, omega 0.1: 3370 ms of short range, 2560 with these.
+__host__ __device__ constexpr int sr_unit_cand(int LP, int LA, int LB) {
+  if (sr_unit_waves(LP, LA, LB) > 1 || LP + LA + LB == 7) return 32;
+  return sr_unit_class(LP, LA, LB) ? 64 : 48;
+}
+// Vectors per lane at which a batch of images is full: more where a contraction costs
+// more.  (With 12 per pass 4, 6 and 10 took 153, 149 and 143 ms for 8 atoms 2x2x2 and
+// 198, 180 and 175 for 5 atoms 2x2x1: a batch's set-up outweighs its even lanes.)
+__host__ __device__ constexpr int sr_unit_fill(int LP, int LA, int LB) {
+  return sr_unit_waves(LP, LA, LB) > 1 ? 10 : 24;
+}
+
 // A lane takes one unit: a pair image n', a BvK cell c1 and a share of the
 // lattice vectors m of that cell.  It sums the Hermite integrals of its
 // vectors in registers, contracts them with the pair's E^ab there, and keeps
@@ -215,6 +227,7 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
   constexpr int RS = NH | 1;                    // odd: the units' sums start in distinct banks
   constexpr int NE = e_off(LB, LA, LB + 1);     // nonzero E coefficients per axis
   constexpr int NHAB = nherm(LAB);
+  constexpr int kUnitCand = sr_unit_cand(LP, LA, LB), kUnitFill = sr_unit_fill(LP, LA, LB);
   constexpr int NBUF = kUnitCand * 32 > 64 * kUnitFl ? kUnitCand * 32 : 64 * kUnitFl;
   struct WaveLds {
     double buf[NBUF];  // candidate lists [entry][lane]; flush values [component][lane]
@@ -553,12 +566,27 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
         }
         wave_sync();  // (the constants below are read again, not kept over the loop)
         s_cnt[lane] += (unsigned)nt;
-        s_cnt[64 + lane] += (unsigned)(nt > 0);
+        if constexpr (!WIDE) s_cnt[64 + lane] += (unsigned)(nt > 0);
         if constexpr (WIDE) {
+          // The lanes of a unit are added up first (in a fixed order), its first lane
+          // (share 0) contracts: (d|dd) and (f|dd) of 8 atoms 2x2x2, omega 0.1, took 559
+          // and 547 ms with a contraction per lane and 12 vectors, 214 and 193 like this.
+          int has = nt > 0;
+          for (int o = 1; __any(lpu > o); o <<= 1) {
+            const bool on = share + o < lpu;
+            const int up = __shfl_down(has, o * ncb, 64);
+            has |= on ? up : 0;
+            static_for<0, NH>([&](auto I) {
+              const double v = __shfl_down(Rb[decltype(I)::v], o * ncb, 64);
+              Rb[decltype(I)::v] += on ? v : 0.0;
+            });
+          }
+          has &= (int)(share == 0);
+          s_cnt[64 + lane] += (unsigned)has;
           // A few rows at a time: their lanes put the Hermite sums and E^ab (with
           // the prefactor in the x rows) into LDS, then lane (cell, tau) gathers
           // R[h + tau] of every row of its part and adds its NAB components.
-          const unsigned long long bal = __ballot(nt > 0);
+          const unsigned long long bal = __ballot(has);
           const int RP = min(max(kWideUnits / ncb, 1), kWideRows);
           const double cK = tcl[6] * Kab, tb = tcl[1] - 1.0, oo2p = 0.5 * tcl[0], t1 = tcl[1];
           double sc = 1.0;  // (1/2g)^{(lP + |tau|)/2} of the lane's tau
@@ -568,7 +596,7 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
           for (int r0 = 0; r0 < rows; r0 += RP) {
             if (!((bal >> (r0 * ncb)) & ((r0 + RP) * ncb >= 64 ? ~0ull : ((1ull << (RP * ncb)) - 1ull)))) continue;
             wave_sync();
-            if (row >= r0 && row < r0 + RP && lane_on) {
+            if (row >= r0 && row < r0 + RP && lane_on && share == 0) {
               double *Ru = sl.R + ((row - r0) * ncb + gl) * RS;
               static_for<0, NH>([&](auto I) { Ru[decltype(I)::v] = Rb[decltype(I)::v]; });
               if (gl == 0) {
