@@ -51,7 +51,7 @@ def flags():
             "-Wno-unused-command-line-argument"]
 
 
-def check_assembly(path: str, kernels: bool) -> int:
+def check_assembly(path: str) -> int:
     """Refuse device code in which a per-lane instruction precedes an exec restore
     (asm_check), or whose text the check no longer understands."""
     with open(path) as fh:
@@ -60,7 +60,7 @@ def check_assembly(path: str, kernels: bool) -> int:
         raise RuntimeError(f"{path}: per-lane instructions in front of an exec restore, where the lanes that left a "
                            "divergent region lose the value (fewer live registers in the kernel, or another "
                            "compiler):\n" + "\n".join(f"  {f}, line {n}: {i}" for f, n, i in found))
-    if kernels and restores == 0:
+    if restores == 0:
         raise RuntimeError(f"{path}: no exec restore found; the check of the assembly does not read it")
     return restores
 
@@ -70,16 +70,20 @@ def _compile(src: str, defs=()) -> str:
     tmp = os.path.join(BUILD, "tmp_" + src.replace(".", "_"))
     shutil.rmtree(tmp, ignore_errors=True)
     os.makedirs(tmp)
-    # the device code is assembled from the text that -save-temps leaves
+    # the device code is assembled from the text that -save-temps leaves (capi.cpp has
+    # none, and its host code is not put through a text)
+    kernels = src.endswith(".hip")
     tobj = os.path.join(tmp, os.path.basename(obj))
-    cmd = [hipcc(), *flags(), *defs, "-save-temps=obj", "-x", "hip", "-c", os.path.join(CSRC, src), "-o", tobj]
+    cmd = [hipcc(), *flags(), *defs, *(["-save-temps=obj"] if kernels else []), "-x", "hip", "-c",
+           os.path.join(CSRC, src), "-o", tobj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
-    asm = glob.glob(os.path.join(tmp, f"*-hip-amdgcn-amd-amdhsa-{ARCH}*.s"))
-    if len(asm) != 1:
-        raise RuntimeError(f"{src}: expected one device assembly text under {tmp}, found {len(asm)}")
-    check_assembly(asm[0], src.endswith(".hip"))
+    if kernels:
+        asm = glob.glob(os.path.join(tmp, f"*-hip-amdgcn-amd-amdhsa-{ARCH}*.s"))
+        if len(asm) != 1:
+            raise RuntimeError(f"{src}: expected one device assembly text under {tmp}, found {len(asm)}")
+        check_assembly(asm[0])
     os.replace(tobj, obj)
     shutil.rmtree(tmp)
     return obj

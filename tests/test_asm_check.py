@@ -68,9 +68,9 @@ def test_build_refuses(tmp_path):
     f = tmp_path / "k.s"
     f.write_text(REGION.format(COPY))
     with pytest.raises(RuntimeError, match="v_accvgpr_write_b32 a6, v40"):
-        build.check_assembly(str(f), True)
+        build.check_assembly(str(f))
     f.write_text(REGION.format(""))
-    assert build.check_assembly(str(f), True) == 1
+    assert build.check_assembly(str(f)) == 1
     f.write_text("nothing that the check reads\n")
     with pytest.raises(RuntimeError, match="no exec restore"):
-        build.check_assembly(str(f), True)
+        build.check_assembly(str(f))
