@@ -71,5 +71,10 @@ inline PairFtShape pairft_shape(int64_t nx, int nq, int qpmax) {
   while (qp > 1 && nx * ((nq + 64 * qp - 1) / (64 * qp)) < 8192) qp /= 2;
   return {qp, 0, 1};
 }
+// blocks of q of a launch (grid y, at most 65535)
+inline int64_t pairft_blocks(const PairFtShape &s, int nq) {
+  const int64_t per = s.nql ? s.nql : 64 * s.qp;
+  return (nq + per - 1) / per;
+}
 
 }  // namespace rsgdf

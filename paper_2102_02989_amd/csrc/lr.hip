@@ -399,11 +399,10 @@ void pairft_launch(const PairFTParams &pp, int pbeg, int64_t nx, const PairFtSha
     PairFTParams ps = pp;
     ps.nql = sh.nql;
     hipLaunchKernelGGL((pairft_binned_kernel<LA, LB, 1, true>),
-                       dim3((unsigned)nx, (unsigned)((pp.nq + sh.nql - 1) / sh.nql)), dim3(64 * sh.waves), 0, stream, ps,
-                       pbeg);
+                       dim3((unsigned)nx, (unsigned)pairft_blocks(sh, pp.nq)), dim3(64 * sh.waves), 0, stream, ps, pbeg);
   } else if (sh.qp == QP) {
     hipLaunchKernelGGL((pairft_binned_kernel<LA, LB, QP, false>),
-                       dim3((unsigned)nx, (unsigned)((pp.nq + 64 * QP - 1) / (64 * QP))), dim3(64), 0, stream, pp, pbeg);
+                       dim3((unsigned)nx, (unsigned)pairft_blocks(sh, pp.nq)), dim3(64), 0, stream, pp, pbeg);
   } else if constexpr (QP > 1) {
     pairft_launch<LA, LB, QP / 2>(pp, pbeg, nx, sh, stream);
   }
@@ -416,7 +415,7 @@ hipError_t launch_pairft_binned(const PairFTParams &pp, hipStream_t stream) {
     const int64_t nx = (int64_t)(pp.pgrp[g + 1] - pp.pgrp[g]) * pp.nk;
     if (nx == 0) continue;
     const PairFtShape sh = pairft_shape(nx, pp.nq, pairft_qpl(la_of[g], lb_of[g]));
-    if (nx > 0x7fffffff || (pp.nq + 63) / 64 > 65535) return hipErrorInvalidConfiguration;
+    if (nx > 0x7fffffff || pairft_blocks(sh, pp.nq) > 65535) return hipErrorInvalidConfiguration;
     switch (g) {
       case 0: pairft_launch<2, 2, pairft_qpl(2, 2)>(pp, pp.pgrp[g], nx, sh, stream); break;
       case 1: pairft_launch<2, 1, pairft_qpl(2, 1)>(pp, pp.pgrp[g], nx, sh, stream); break;

@@ -1,5 +1,5 @@
-"""Host tests of the rules by which the short-range kernel deals out its lanes
-(csrc/lanes.h), compiled for the CPU."""
+"""Host tests of the rules by which the short-range kernel and the pair transforms deal
+out their lanes (csrc/lanes.h), compiled for the CPU."""
 import ctypes
 
 import numpy as np
@@ -31,6 +31,9 @@ extern "C" long box_errors(int dim0, int dim1, int dim2, int near) {
       bad += a != q / d12 || b != q / dim2 % dim1 || c != q % dim2;
     }
   return bad;
+}
+extern "C" long pairft_blocks(long nx, int nq, int la, int lb) {
+  return rsgdf::pairft_blocks(rsgdf::pairft_shape(nx, nq, rsgdf::pairft_qpl(la, lb)), nq);
 }
 """
 
@@ -86,3 +89,12 @@ def test_box_entries(lanes, dims):
     entry near a plane's end has the indices of the whole-number division."""
     lanes.box_errors.restype = ctypes.c_long
     assert lanes.box_errors(*dims, min(4 * dims[2] + 200, dims[1] * dims[2])) == 0
+
+
+@pytest.mark.parametrize("la,lb,width", [(0, 0, 8), (1, 0, 4), (1, 1, 2), (2, 1, 2), (2, 2, 1)])
+def test_pair_transform_grid(lanes, la, lb, width):
+    """A class of up to 65535 blocks of 64 width q is one launch, down to one pair."""
+    lanes.pairft_blocks.restype = ctypes.c_long
+    for nx in (1, 21, 10000):
+        assert lanes.pairft_blocks(ctypes.c_long(nx), 65535 * 64 * width, la, lb) == 65535
+        assert lanes.pairft_blocks(ctypes.c_long(nx), 65535 * 64 * width + 1, la, lb) == 65536
