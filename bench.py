@@ -50,8 +50,10 @@ TRAFFIC_FILES = {  # committed FETCH_SIZE / WRITE_SIZE summaries, by kernel fami
 }
 KERNEL_SOURCES = {
     "sr": ("paper_2102_02989_amd/csrc/sr3c.hip", "paper_2102_02989_amd/csrc/device_math.h",
-           "paper_2102_02989_amd/csrc/plan.h", "paper_2102_02989_amd/csrc/boys.h"),
-    "lr_gemm": ("paper_2102_02989_amd/csrc/lr.hip", "paper_2102_02989_amd/csrc/kernels.h"),
+           "paper_2102_02989_amd/csrc/plan.h", "paper_2102_02989_amd/csrc/boys.h",
+           "paper_2102_02989_amd/csrc/lanes.h"),
+    "lr_gemm": ("paper_2102_02989_amd/csrc/lr.hip", "paper_2102_02989_amd/csrc/kernels.h",
+                "paper_2102_02989_amd/csrc/lanes.h"),
 }
 TABLE_S3 = ("paper Table S3 (J+K CPU time per SCF cycle including DF initialisation, one core of an Intel Xeon "
             "Gold 6126 at 2.6 GHz, 16 GB): diamond/cc-pVDZ N_k = 3^3: GDF 1441.77 s, RSGDF 205.25 s; "
@@ -275,7 +277,7 @@ def main():
     achieved = flops / (t_gemm * 1e-3) if t_gemm > 0 else 0.0
     roof_gemm = {"bound": "mfma", "achieved": achieved / 1e12, "peak": PEAK[lr_name] / 1e12, "unit": "TFLOP/s",
                  "frac": achieved / PEAK[lr_name], "traffic": recorded_traffic("lr_gemm", problem.name),
-                 "kernel": (f"{'lr_gemm_f16x3_kernel' if lr_name == 'f16x3' else 'lr_gemm_tiled_kernel'} "
+                 "kernel": (f"lr_gemm_{'f64' if lr_name == 'fp64' else 'f32' if lr_name == 'fp32' else 'f16x3'}_kernel "
                             f"({lr_name} complex G-space contraction, all k12 classes of one build; flops = 8 per "
                             f"complex multiply-add" + (", the form issues 24 FP16 flops per complex multiply-add"
                                                        if lr_name == "f16x3" else "") + ")"),
@@ -285,7 +287,7 @@ def main():
     roof_sr = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP64_VECTOR / 1e12, "unit": "TFLOP/s",
                "frac": achieved / PEAK_FP64_VECTOR, "traffic": recorded_traffic("sr", problem.name),
                "kernel": "sr3c_unit_kernel (the 24 angular-momentum classes of one build, on 3 side streams; flops = "
-                         "image-loop terms plus the Hermite contractions)",
+                         "image-loop terms plus the Hermite contractions performed)",
                "flops_per_launch": flops, "avg_launch_ms": t_sr}
     # the dominant kernel family by time; the other one is reported beside it
     roof, roof2 = (roof_gemm, roof_sr) if t_gemm > t_sr else (roof_sr, roof_gemm)

@@ -2124,8 +2124,8 @@ int tune_trial(const rsgdf_cell *cell, const rsgdf_basis *basis, const rsgdf_bas
 }  // namespace
 
 // Batch of cells: the SR work items of all cells are merged into one launch
-// per angular-momentum class (a cost-sorted (cell, item) queue drained by the
-// hardware dispatcher); reduce, fold and the long-range part follow per cell.
+// per angular-momentum class (a (cell, item) queue drained by the hardware
+// dispatcher, the cells in turn, each cell's items heaviest first); reduce, fold and the long-range part follow per cell.
 // The whole device sequence is captured once into a graph and replayed.
 struct rsgdf_batch {
   std::vector<std::unique_ptr<Job>> jobs;
@@ -2280,7 +2280,7 @@ int rsgdf_batch_create(int32_t ncell, const rsgdf_cell *cells, const rsgdf_basis
       for (auto &j : B->jobs) j->ybuf = B->d_Y.as<double>();
     }
   }
-  // merged SR queue: per class, all cells' items, heaviest first
+  // merged SR queue: per class, the cells in turn, each cell's items heaviest first
   std::vector<SRParams> prms;
   std::vector<SRWork> work;
   B->cls_off.assign(1, 0);
