@@ -568,20 +568,26 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
         s_cnt[lane] += (unsigned)nt;
         if constexpr (!WIDE) s_cnt[64 + lane] += (unsigned)(nt > 0);
         if constexpr (WIDE) {
-          // The lanes of a unit are added up first (in a fixed order), its first lane
-          // (share 0) contracts: (d|dd) and (f|dd) of 8 atoms 2x2x2, omega 0.1, took 559
-          // and 547 ms with a contraction per lane and 12 vectors, 214 and 193 like this.
+          // Where that leaves at least two rows fewer to contract, the lanes of a unit
+          // are added up first (in a fixed order) and its first lane (share 0) contracts:
+          // (d|dd) and (f|dd) of 8 atoms 2x2x2, omega 0.1, took 559 and 547 ms with a
+          // contraction per lane and 12 vectors, 214 and 193 like this.
+          const unsigned long long cells = (1ull << ncb) - 1ull;
           int has = nt > 0;
-          for (int o = 1; __any(lpu > o); o <<= 1) {
-            const bool on = share + o < lpu;
-            const int up = __shfl_down(has, o * ncb, 64);
-            has |= on ? up : 0;
-            static_for<0, NH>([&](auto I) {
-              const double v = __shfl_down(Rb[decltype(I)::v], o * ncb, 64);
-              Rb[decltype(I)::v] += on ? v : 0.0;
-            });
+          const unsigned long long any = __ballot(has);
+          const int act_rows = __popcll(__ballot(gl == 0 && lane_on && ((any >> (row * ncb)) & cells)));
+          if (act_rows >= m + 2) {
+            for (int o = 1; __any(lpu > o); o <<= 1) {
+              const bool on = share + o < lpu;
+              const int up = __shfl_down(has, o * ncb, 64);
+              has |= on ? up : 0;
+              static_for<0, NH>([&](auto I) {
+                const double v = __shfl_down(Rb[decltype(I)::v], o * ncb, 64);
+                Rb[decltype(I)::v] += on ? v : 0.0;
+              });
+            }
+            has &= (int)(share == 0);
           }
-          has &= (int)(share == 0);
           s_cnt[64 + lane] += (unsigned)has;
           // A few rows at a time: their lanes put the Hermite sums and E^ab (with
           // the prefactor in the x rows) into LDS, then lane (cell, tau) gathers
@@ -592,11 +598,10 @@ void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restric
           double sc = 1.0;  // (1/2g)^{(lP + |tau|)/2} of the lane's tau
 #pragma unroll
           for (int i = 0; i < LP; ++i) sc *= (i < LP - 1 || tau2 < NCP) ? tcl[8] : 1.0;
-          const unsigned long long cells = (1ull << ncb) - 1ull;
           for (int r0 = 0; r0 < rows; r0 += RP) {
             if (!((bal >> (r0 * ncb)) & ((r0 + RP) * ncb >= 64 ? ~0ull : ((1ull << (RP * ncb)) - 1ull)))) continue;
             wave_sync();
-            if (row >= r0 && row < r0 + RP && lane_on && share == 0) {
+            if (row >= r0 && row < r0 + RP && lane_on && ((bal >> (row * ncb)) & cells)) {
               double *Ru = sl.R + ((row - r0) * ncb + gl) * RS;
               static_for<0, NH>([&](auto I) { Ru[decltype(I)::v] = Rb[decltype(I)::v]; });
               if (gl == 0) {
