@@ -173,7 +173,7 @@ __host__ __device__ constexpr int sr_unit_waves(int LP, int LA, int LB) {
 // workgroups that the registers allow their LDS (one of 108 to 159 KB per CU where a
 // lane has the registers of a SIMD to itself, else two of 76 KB).  With 12 in every class
 // the contractions, one per pass, were the work where a unit has hundreds of vectors:
-// 8 atoms 2x2x2, omega 0.1: 3370 ms of short range, 2560 with these.
+// 8 atoms 2x2x2, omega 0.1: 3370 ms of short range, 2570 with these.
 __host__ __device__ constexpr int sr_unit_cand(int LP, int LA, int LB) {
   if (sr_unit_waves(LP, LA, LB) > 1 || LP + LA + LB == 7) return 32;
   return sr_unit_class(LP, LA, LB) ? 64 : 48;
@@ -206,13 +206,13 @@ __host__ __device__ constexpr int sr_unit_fill(int LP, int LA, int LB) {
 // wave-cooperative kernel below 126 accumulators (short-range phase): 8 atoms
 // double zeta 2x2x2, omega 0.5: 692 -> 238 ms; 4 atoms 3x3x3, omega 1.5: 646 ->
 // 167 ms; 3 atoms 1x3x2, omega 1: 247 -> 94 ms; 12 atoms single zeta 4x4x4,
-// omega 0.1: 274 -> 89 ms; 2 atoms at Gamma, omega 0.1: 1.51 -> 1.26 ms.
+// omega 0.1: 274 -> 89 ms; 2 atoms at Gamma, omega 0.1: 1.51 -> 1.2 ms.
 //
 // The wide classes ((d|dd), (f|dp), (f|dd)) would need 234 to 468 accumulators a
 // lane.  Their sums cross LDS: 16 units at a time, whose R_tuv the lanes of
 // (cell, tau) gather at h + tau, each keeping its NAB components in registers.
 // With the cooperative kernel for these three the first three workloads above
-// were 238, 167 and 94 ms; they are 144, 109 and 58 ms.
+// were 238, 167 and 94 ms; they are 139, 101 and 37 ms.
 template <int LP, int LA, int LB>
 __global__ __launch_bounds__(64 * kUnitWaves) __attribute__((amdgpu_waves_per_eu(sr_unit_waves(LP, LA, LB))))
 void sr3c_unit_kernel(const SRParams *__restrict__ prms, const SRWork *__restrict__ works,
